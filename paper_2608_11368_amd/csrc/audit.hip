@@ -1,117 +1,104 @@
 // Frozen-population estimator audit (paper Sec. 6.2, Table 2; App. D
-// metrics MSE = E||g^ - g_full||^2 and the bias norm).
+// metrics MSE = E||g^ - g_full||^2 and the bias norm) and its
+// update-direction column.
 //
 // The complete-pair target of a prompt is itself a combination of its score
 // rows, t = a S_b with a = (r_i - mean r)/(G - 1) (Theorem 1), and each
-// replicate's HT estimate is g_r = A~^(r) S_b (Eq. pair-advantage).  So the
-// deviation is a single contraction,
-//     g_r - t = (A~^(r) - a) S_b = delta_r S_b,
-// and the audit needs e_r = ||delta_r S_b||^2 for every replicate r plus
-// ||delta_bar S_b|| for the bias (delta_bar = mean_r delta_r).
+// replicate's HT estimate is g_r = u_r S_b with u_r = A~^(r) (Eq.
+// pair-advantage).  With delta_r = u_r - a and the Gram matrix K = S_b S_b^T,
+//     e_r   = ||g_r - t||^2 = delta_r K delta_r^T,
+//     bias  = ||mean_r g_r - t|| = sqrt(delta_bar K delta_bar^T),
+//     cos_r = <g_r, t> / (|g_r| |t|) = u_r K a / sqrt(u_r K u_r * a K a),
+// so the score rows are needed once, for K, and a replicate costs G^2
+// operations instead of 2 G D.  K is formed from exact bf16 products with
+// fp32 sums of at most a slice's columns, everything after it is fp64: e_r is
+// within about 1e-7 of 64-bit arithmetic for score rows that do not nearly
+// cancel in delta_r S_b, and the error grows with the square of that
+// cancellation, |delta|.|s| over |delta S|.  Contracting delta_r S_b column by
+// column on the fp16 matrix cores (the form before) gave 3e-4 and grew
+// linearly, so it is behind until the rows cancel by a factor of 10^4; at
+// B = 256, G = 16, D = 65536, R = 4096 it took 1.75 ms, bound by the
+// matrix cores and the FP32 squares of their output.
 //
 // Pipeline (all on the caller's stream):
-//  1. audit_coeffs  one workgroup per (prompt, 256 replicates), one lane per
-//                   replicate: Philox draw of J^(r) (same counter reading as
-//                   the design draw), the coefficient fold over a per-prompt
-//                   table W_ij = (r_i - r_j)/rho_ij in LDS, centring over the
-//                   completed vertices, delta_r stored in fp32, and a
-//                   fixed-order partial sum of delta over the 256 lanes.
-//  2. audit_prep    replicate rows padded with zero rows to a whole number
-//                   of tile pairs (R rounded up to 64), delta_bar stored
-//                   in the row after them.  One extra workgroup lists the
-//                   live prompts in ascending order: those whose rewards are
-//                   not all equal.  A prompt with equal rewards has
-//                   W = 0 and a = 0, so every delta_r is exactly zero and so
-//                   are its e_r, MSE and bias; the matrix-core grid covers
-//                   the live prompts only.
-//  3. audit_mfma    the contraction on v_mfma_f32_32x32x16_f16.  Each score
-//                   row of a column slice is rescaled by 2^-e_i, with e_i
-//                   the exponent of the row's largest magnitude within the
-//                   slice, and rounded to fp16 (to nearest), which is exact
-//                   for every entry within 2^17 of that maximum and off by
-//                   at most 2^-25 of it below (8 significant bits fit in
-//                   11, down to fp16's subnormals); each
-//                   replicate row of delta is rescaled by 2^(e_i - f_r), with
-//                   f_r chosen so its largest entry lies in [1, 2), and rounded
-//                   once to fp16 (2^-11 relative).  The products are
-//                   rescalings of delta_r S_b by 2^-f_r, so e_r = 4^f_r * sum
-//                   of squares.
-//                   A workgroup owns one prompt and one slice of score
-//                   columns: the slice is converted once into LDS and every
-//                   replicate row sweeps over it, so S_b is read from HBM
-//                   once; the squares of every output tile are summed in the
-//                   epilogue and the rows x D product is never written.
-//                   The live (prompt, slice) pairs are split evenly over the
-//                   8 XCDs, each XCD taking a contiguous range, so the
-//                   workgroups of a prompt share that XCD's L2 for its delta
-//                   rows.  The
-//                   delta_bar row is one fp32 dot product per score column
-//                   on the vector units against the same LDS slice.
-//  4. audit_sqerr   e_r = per-slice partial sums reduced in fixed order, one
-//                   thread per (prompt, replicate), exactly 0 for a prompt
-//                   that is not live; fp64 partial sums of e_r
-//     audit_final   per prompt: MSE = fp64 mean of e_r, bias = sqrt(e of the
-//                   delta_bar row).
+//  1. audit_stream  one workgroup per (prompt, column slice): the slice's
+//                   partial Gram matrix, bound by HBM, and with the score
+//                   loads in flight its share of the prompt's design draws,
+//                   which are bound by the integer multiplies of Philox:
+//                   J^(r) of each replicate as a 64-bit word.  Prompts whose
+//                   rewards are all equal have delta_r = 0 in every
+//                   replicate: their rows are not read.
+//  2. audit_tables  one workgroup per prompt: the slice partials added in
+//                   order into K (fp64), the rule's edge table, the target's
+//                   coefficients, the status checks.
+//  3. audit_eval    64 replicates per wave: the fold of their indicators over
+//                   the edge table (fp32 matrix instructions) and the
+//                   quadratic form (fp64 matrix instructions).
+//  4. audit_final   one wave per prompt: MSE, bias, or the mean cosine.
 #include "common.hpp"
+#include "gram.hpp"
 #include "launch.hpp"
 
 namespace pair {
 
 namespace {
 
-typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-constexpr int kCoefThreads = 256;    // replicates per audit_coeffs workgroup
-constexpr int kSqThreads = 256;      // replicates per audit_sqerr workgroup
-constexpr int kMfmaThreads = 512;    // 8 waves per workgroup
-constexpr int kMfmaWaves = kMfmaThreads / kWave;
-constexpr int kTile = 32;            // replicate rows (and score columns) per matrix instruction
-constexpr int kPair = 2;             // replicate tiles a wave carries at once
-
-// Score columns per workgroup slice: the slice of S_b (16 * ks rows, fp16,
-// plus one skew row per 8) stays resident in LDS while all replicate rows
-// sweep over it.
-constexpr int slice_cols(int ks) { return ks == 1 ? 2048 : (ks == 2 ? 1024 : 512); }
+constexpr int kEvalThreads = 256;
+constexpr int kTableThreads = 256;
+constexpr int64_t kMaxSlices = 128;   // score-column slices per prompt at most
+constexpr int64_t kDrawRun = 512;     // replicates a stream workgroup draws at most, about
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct AuditLayout {
-  int ks;            // 16-wide K steps (ceil(gmax / 16))
-  int kp;            // 16 * ks: padded K extent
-  int64_t rbar;      // the delta_bar row: R rounded up to whole pairs of tiles
-  int64_t ntiles;    // 32-row tiles per prompt: rbar / 32 replicate tiles + the delta_bar tile
-  int64_t rrows;     // ntiles * 32
-  int64_t nslices;   // score-column slices per prompt
-  int64_t nwg;       // audit_coeffs workgroups per prompt
-  int64_t nsq;       // audit_sqerr workgroups per prompt
-  size_t delta_off, epart_off, dsum_off, rpart_off, ebar_off, live_off, total;
+  int ks, kp;
+  int64_t nsl;     // score-column slices per prompt
+  int64_t slice;   // columns per slice
+  int64_t slots;   // audit_stream workgroups per prompt: nsl slices, and more if R is large
+  int64_t nchunk;  // audit_eval workgroups per prompt
+  int rounds;      // and times 64 replicates each of their waves takes
+  size_t part_off, gex_off, k_off, w_off, v_off, a_off, flag_off, bits_off, epart_off, dpart_off,
+      need;
 };
 
+// The slicing depends on gmax and D alone, so that a prompt's K, and with it
+// e_r, is the same whatever batch or replicate range it is audited in.  A
+// slice is 256 KB of scores where the batch's largest group fills its blocks of
+// 16 rows: the partial it writes is under 5% of that.
 AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   AuditLayout L;
   L.ks = (gmax + 15) / 16;
   L.kp = 16 * L.ks;
-  L.rbar = round_up(R, (int64_t)kPair * kTile);
-  L.ntiles = L.rbar / kTile + 1;
-  L.rrows = L.ntiles * kTile;
-  L.nslices = (D + slice_cols(L.ks) - 1) / slice_cols(L.ks);
-  L.nwg = (R + kCoefThreads - 1) / kCoefThreads;
-  L.nsq = (R + 1 + kSqThreads - 1) / kSqThreads;
+  int64_t nsl = ceil_div(D, (L.ks == 1 ? 4 : (L.ks == 2 ? 2 : 1)) * kGramRoundCols);
+  if (nsl > kMaxSlices) nsl = kMaxSlices;
+  L.slice = round_up(ceil_div(D, nsl), kGramRoundCols);
+  L.nsl = ceil_div(D, L.slice);
+  L.slots = L.nsl > ceil_div(R, kDrawRun) ? L.nsl : ceil_div(R, kDrawRun);
+  // A wave's first 64 replicates cost the latency of its tables, so with many
+  // it takes twice 64 (28.5 us against 26.4 us at B = 256, G = 16, R = 4096;
+  // four times: 28.1 us, the last workgroups run alone).  Groups above 32 have
+  // work enough in 64 (21 us against 34 us at B = 64, G in 2..64, R = 1000).  By
+  // R and gmax alone: the sums' order is the prompt's own.
+  L.rounds = R >= 2048 && L.ks <= 2 ? 2 : 1;
+  L.nchunk = ceil_div(R, (int64_t)L.rounds * kEvalThreads);
   size_t off = 0;
-  L.delta_off = off;
-  off += (size_t)round_up(B * L.rrows * L.kp * 4, 256);            // fp32 delta rows
-  L.epart_off = off;
-  off += (size_t)round_up(B * L.nslices * L.rrows * 4, 256);       // per-slice squared errors
-  L.dsum_off = off;
-  off += (size_t)round_up(B * L.nwg * gmax * 4, 256);               // partial delta sums
-  L.rpart_off = off;
-  off += (size_t)round_up(B * L.nsq * 8, 256);                      // fp64 partial sums of e_r
-  L.ebar_off = off;
-  off += (size_t)round_up(B * 4, 256);                              // e of the delta_bar row
-  L.live_off = off;
-  off += (size_t)round_up((2 * B + 1) * 4, 256);                    // live count, list, flags
-  L.total = off;
+  auto take = [&](int64_t bytes) {
+    const size_t at = off;
+    off += (size_t)round_up(bytes, 256);
+    return at;
+  };
+  L.part_off = take(B * L.nsl * gram_tiles(L.ks) * 256 * 4);   // slice partials of K
+  L.gex_off = take(B * L.nsl * (L.kp + 1) * 4);                // their row exponents
+  L.k_off = take(B * L.kp * L.kp * 8);                         // K, fp64
+  L.w_off = take(B * L.kp * L.kp * 4);                         // edge table
+  L.v_off = take(B * L.kp * L.kp * 4);                         // 1/rho (self-normalised rule)
+  L.a_off = take(B * L.kp * 8);                                // target coefficients
+  L.flag_off = take(B * 4);                                    // 1: some rewards differ
+  L.bits_off = take(B * R * 8);                                // indicators
+  L.epart_off = take(B * L.nchunk * 8);                        // sums of e_r (of cos_r)
+  L.dpart_off = take(B * L.nchunk * L.kp * 4);                 // sums of the centred folds
+  L.need = off;
   return L;
 }
 
@@ -131,60 +118,209 @@ __device__ __forceinline__ float complete_pair_coeff(float r_i, int lane, int g)
   return vert ? a_full - tot / (float)g : 0.0f;
 }
 
+// Some reward of the prompt differs from the first (a NaN counts as
+// different).  The whole wave calls it.
+__device__ __forceinline__ bool rewards_differ(const float* __restrict__ rewards, int g, int lane) {
+  const float r_i = lane < g ? rewards[lane] : 0.0f;
+  return __ballot(lane < g && !(r_i == lane_value(r_i, 0))) != 0ull;
+}
+
 // ---------------------------------------------------------------------------
-// 1. Replicate coefficients.  A workgroup owns one prompt and 256 replicates
-//    (one per lane).  The edge table W, the probabilities and the
-//    complete-pair coefficients are built once per workgroup in LDS; each lane
-//    then draws its indicators, folds c_i = sum_j J_j W_ij with W read by
-//    broadcast (W_ii = 0, so no j != i test is needed, and a zero indicator
-//    adds exactly nothing), centres, and keeps its KP deviations in registers.
+// 1. Slice partials of K, and the design draws between their loads.
 // ---------------------------------------------------------------------------
-template <int KP>
-__global__ __launch_bounds__(kCoefThreads) void audit_coeffs_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
-    const float* __restrict__ rewards, const float* __restrict__ p,
-    const float* __restrict__ pi_w, int32_t rule, float wmax, uint64_t seed, int64_t rep0,
-    int64_t pbase, int64_t R, int64_t nwg, int64_t rrows, float* __restrict__ delta,
-    float* __restrict__ dsum, int32_t* __restrict__ edge_count, int32_t* d_status) {
-  constexpr int kWaves = kCoefThreads / kWave;
-  __shared__ __align__(16) float W[KP * KP];     // rule weight x (r_i - r_j), zero on and past G
-  __shared__ __align__(16) float V[KP * KP];     // 1/rho_ij (self-normalised denominator)
-  __shared__ float pl[KP], rl[KP], af[KP];
-  __shared__ float wsum[kWaves][KP];
-  const int64_t b = blockIdx.x / nwg;
-  const int64_t chunk = blockIdx.x - b * nwg;
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, d_status, chunk == 0 && tid == 0)) return;
+template <int KS>
+__global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void audit_stream_kernel(
+    int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t D,
+    const uint16_t* __restrict__ scores, int64_t ld, int nsl, int64_t slice, int slots,
+    const float* __restrict__ rewards, const float* __restrict__ p, uint64_t seed, int64_t rep0,
+    int64_t pbase, int64_t R, int skip_equal, int rescale, float* __restrict__ part,
+    int32_t* __restrict__ gex, uint16_t* __restrict__ bits, int want_counts, int32_t* d_status) {
+  constexpr int KP = 16 * KS;
+  constexpr int kTiles = gram_tiles(KS);
+  __shared__ __align__(16) uint16_t stage[gram_lds_elems(KS)];
+  __shared__ int32_t ex[KP];
+  __shared__ uint64_t threshold[KP];
+  const int slot = (int)(blockIdx.x % (uint32_t)slots);
+  const int64_t b = blockIdx.x / (uint32_t)slots;
+  int64_t o0, g64;
+  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
+  const int g = (int)g64;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const bool wanted = !skip_equal || rewards_differ(rewards + o0, g, lane);
+  if (!wanted && !want_counts) return;
+  if (tid < KP) {
+    const float pv = tid < g ? p[o0 + tid] : 0.0f;
+    threshold[tid] = p_in_range(pv) ? inclusion_threshold(pv) : 0ull;
+  }
+  __syncthreads();
+
+  // This wave's draws: items of 64 replicates (lane = replicate) and 16
+  // vertices, dealt to the prompt's waves in turn.  One unit is one Philox
+  // block (four vertices) of one item; an item is 16 bits of the word.
+  const int ngrp = (g + 15) / 16;
+  const int stride = slots * kGramWaves;
+  const int nitems = (int)((R + kWave - 1) / kWave) * ngrp;
+  int item = slot * kGramWaves + wave;
+  const int units = item < nitems ? 4 * ((nitems - item + stride - 1) / stride) : 0;
+  int done = 0;
+  uint32_t word = 0;
+  PhiloxRep rep;
+  auto draw_until = [&](int target) {
+    for (; done < target; ++done) {
+      // item / ngrp for ngrp = 1 .. 4
+      const int batch = ngrp == 3 ? (int)(__umulhi((uint32_t)item, 0xAAAAAAABu) >> 1)
+                                  : item >> (ngrp >> 1);
+      const int grp = item - batch * ngrp;
+      const int64_t r = (int64_t)batch * kWave + lane;
+      const int sub = done & 3, quad = 4 * grp + sub;
+      if (sub == 0) {
+        rep = philox_rep((uint64_t)(rep0 + r));
+        word = 0;
+      }
+      if (4 * quad < g) {
+        const Philox4x64 x = philox_quad(rep, (uint64_t)(pbase + b), (uint64_t)quad, seed);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)   // the threshold is 0 past the group
+          word |= (x.w[q] >> 32) < threshold[4 * quad + q] ? 1u << (4 * sub + q) : 0u;
+      }
+      if (sub == 3) {
+        if (r < R) bits[(b * R + r) * 4 + grp] = (uint16_t)word;
+        item += stride;
+      }
+    }
+  };
+  if (wanted && slot < nsl) {
+    const int64_t c_lo = slot * slice;
+    const int64_t c_hi = c_lo + slice < D ? c_lo + slice : D;
+    gram_slice_of<KS, false>(
+        scores + o0 * ld, ld, g, c_lo, c_hi, stage, ex, rescale != 0,
+                      part + (b * nsl + slot) * (kTiles * 256),
+                      gex + (b * nsl + slot) * (KP + 1), d_status, [&](int k, int n) {
+                        draw_until(k + 1 < n ? (int)((float)units * (float)(k + 1) / (float)n)
+                                             : units);
+                      });
+  }
+  draw_until(units);
+}
+
+// ---------------------------------------------------------------------------
+// 2. Per-prompt tables: K, the edge table W_ij (the rule's weight times
+//    r_i - r_j, zero on the diagonal and past G), 1/rho for the
+//    self-normalised rule, the target's coefficients a, and for the cosine
+//    K a and a K a.  The G x G tables are stored as the fragments that
+//    audit_eval's matrix instructions take as their A operand (16 x 4: lane l
+//    holds row l % 16 and column l / 16).  Step S of a row block covers the
+//    columns 16 (S / 4) + 4 (l / 16) + S % 4, so that four consecutive
+//    vertices of a lane group meet in four consecutive steps.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ int frag_column(int step, int lane) {
+  return 16 * (step >> 2) + 4 * (lane >> 4) + (step & 3);
+}
+
+// The fp64 instruction leaves row 4 v + q of its result in accumulator v of
+// lane group q, the fp32 one row 4 q + v: rows of K go in transposed, so that
+// both leave vertex 4 q + v there.  It is its own inverse.
+__device__ __forceinline__ int frag_row64(int row) { return 4 * (row & 3) + (row >> 2); }
+
+// Place of K_ij in the fragments of a prompt.
+__device__ __forceinline__ int frag_place64(int kp, int i, int j) {
+  const int step = 4 * (j >> 4) + (j & 3), lane = 16 * ((j & 15) >> 2) + frag_row64(i & 15);
+  return ((i >> 4) * (kp / 4) + step) * kWave + lane;
+}
+
+// One workgroup per prompt for the edge table and one per tile of K.
+template <int KS>
+__global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
+    int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
+    const float* __restrict__ rewards, const float* __restrict__ p, const float* __restrict__ pi_w,
+    int32_t rule, float wmax, int64_t nsl, int skip_equal, const float* __restrict__ part,
+    const int32_t* __restrict__ gex, double* __restrict__ K, float* __restrict__ wt,
+    float* __restrict__ vt, double* __restrict__ a_out, int32_t* __restrict__ flag,
+    int32_t* d_status) {
+  constexpr int KP = 16 * KS;
+  constexpr int kTiles = gram_tiles(KS);
+  __shared__ float pl[KP], rl[KP];
+  const int64_t b = blockIdx.x / (kTiles + 1);
+  const int t = (int)(blockIdx.x - b * (kTiles + 1)) - 1;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  int64_t o0, g64;
+  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, d_status, t < 0 && tid == 0)) return;
+  const int g = (int)g64;
+
+  if (t >= 0) {
+    // Thread e holds entry e of the tile; the slices are added in order,
+    // sixteen loads in flight.  The stream leaves no partials for a prompt
+    // of equal rewards, and nothing reads its K.
+    if (skip_equal && !rewards_differ(rewards + o0, g, lane)) return;
+    int a = 0, c = 0;
+#pragma unroll
+    for (int x = 0; x < KS; ++x)
+#pragma unroll
+      for (int y = x; y < KS; ++y)
+        if (gram_tile(KS, x, y) == t) {
+          a = x;
+          c = y;
+        }
+    const int i = 16 * a + 4 * (tid >> 6) + (tid & 3), j = 16 * c + ((tid >> 2) & 15);
+    const float* src = part + (b * nsl * kTiles + t) * 256 + tid;
+    const int32_t* gx = gex + b * nsl * (KP + 1);
+    double k = 0.0;
+    const bool inside = 16 * c < g;   // uniform; entries past g inside a block are 0
+    for (int64_t s0 = 0; inside && s0 < nsl; s0 += 16) {
+      float v[16];
+      int32_t scaled[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const bool in = s0 + q < nsl;
+        v[q] = in ? src[(s0 + q) * (kTiles * 256)] : 0.0f;
+        scaled[q] = (in && skip_equal) ? gx[(s0 + q) * (KP + 1) + KP] : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        double x = (double)v[q];
+        if (scaled[q] != 0) {
+          const int32_t* row = gx + (s0 + q) * (KP + 1);
+          // rows past the prompt's own blocks have no exponent
+          x = i < g && j < g ? ldexp(x, row[i] + row[j]) : 0.0;
+        }
+        k += x;
+      }
+    }
+    if (!skip_equal && !isfinite(k)) raise_status(d_status, PAIR_ST_NONFINITE);
+    K[b * (KP * KP) + frag_place64(KP, i, j)] = k;
+    if (a != c) K[b * (KP * KP) + frag_place64(KP, j, i)] = k;
+    return;
+  }
 
   if (wave == 0) {
     const bool vert = lane < g;
     const float r_i = vert ? rewards[o0 + lane] : 0.0f;
     const float p_i = vert ? p[o0 + lane] : 1.0f;
+    if (vert && !p_in_range(p_i)) raise_status(d_status, PAIR_ST_P_RANGE);
+    const float a_full = complete_pair_coeff(r_i, lane, g);
     if (lane < KP) {
       pl[lane] = p_i;
       rl[lane] = r_i;
+      a_out[b * KP + lane] = (double)a_full;
     }
-    if (vert && !p_in_range(p_i) && chunk == 0) raise_status(d_status, PAIR_ST_P_RANGE);
-    const float a_full = complete_pair_coeff(r_i, lane, (int)g);
-    if (lane < KP) af[lane] = a_full;
+    const bool differ = __ballot(vert && !(r_i == lane_value(r_i, 0))) != 0ull;
+    if (lane == 0) flag[b] = differ ? 1 : 0;
   }
   __syncthreads();
-
   bool bad_rho = false;
-  for (int idx = tid; idx < KP * KP; idx += kCoefThreads) {
-    const int i = idx / KP, j = idx - i * KP;
+  for (int idx = tid; idx < KP * KP; idx += kTableThreads) {
+    const int fl = idx & (kWave - 1), blk = idx / kWave;
+    const int i = 16 * (blk / (KP / 4)) + (fl & 15), j = frag_column(blk % (KP / 4), fl);
     float w = 0.0f, v = 0.0f;
     if (i != j && i < g && j < g) {
       float rho, pii = pl[i], pij = pl[j];
       if (pi_w != nullptr) {
-        const float* blk = pi_w + b * (int64_t)gmax * gmax;
+        const float* blk_w = pi_w + b * (int64_t)gmax * gmax;
         const int lo = i < j ? i : j, hi = i < j ? j : i;
-        rho = blk[lo * gmax + hi];
-        pii = blk[i * gmax + i];
-        pij = blk[j * gmax + j];
+        rho = blk_w[lo * gmax + hi];
+        pii = blk_w[i * gmax + i];
+        pij = blk_w[j * gmax + j];
       } else {
         rho = pl[i] * pl[j];
       }
@@ -195,703 +331,549 @@ __global__ __launch_bounds__(kCoefThreads) void audit_coeffs_kernel(
         bad_rho = true;
       }
     }
-    W[idx] = w;
-    V[idx] = v;
+    wt[b * (KP * KP) + idx] = w;
+    if (rule == PAIR_RULE_SELFNORM) vt[b * (KP * KP) + idx] = v;
   }
-  if (bad_rho && chunk == 0) raise_status(d_status, PAIR_ST_RHO_RANGE);
-  __syncthreads();
-
-  // Indicators of this lane's replicate.
-  const int64_t rloc = chunk * kCoefThreads + tid;
-  const bool valid = rloc < R;
-  uint64_t bits = 0;
-  if (valid) {
-    const uint64_t rg = (uint64_t)(rep0 + rloc);
-    for (int blk = 0; blk * 4 < g; ++blk) {
-      const Philox4x64 x =
-          philox4x64_10(rg, (uint64_t)(pbase + b), (uint64_t)blk, 0ull, seed, 0ull);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = blk * 4 + q;
-        if (i < g) {
-          const float pv = pl[i];
-          const uint64_t u = x.w[q] >> 32;
-          if (p_in_range(pv) && u < inclusion_threshold(pv)) bits |= 1ull << i;
-        }
-      }
-    }
-  }
-  const int k = __popcll(bits);
-  if (valid && edge_count != nullptr) edge_count[b * R + rloc] = k * (k - 1) / 2;
-  if (k < 2) bits = 0;   // fewer than two completed vertices: A~ = 0
-
-  // Fold: A~_i = J_i (1/(2N)) sum_j J_j W_ij, in ascending j; then centre over
-  // the completed vertices (not for the marginal-only rule, whose fold is not
-  // antisymmetric).  2N = G (G - 1), or k (k - 1) for the observed-edge mean,
-  // or sum_{i, j observed} 1/rho_ij for the self-normalised rule.
-  float m[KP], d[KP];
-#pragma unroll
-  for (int j = 0; j < KP; ++j) m[j] = ((bits >> j) & 1ull) ? 1.0f : 0.0f;
-  float den = (float)(g * (g - 1));
-  if (rule == PAIR_RULE_RATIO_KE) den = (float)(k * (k - 1));
-  if (rule == PAIR_RULE_SELFNORM) {
-    float n2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < KP; ++i) {
-      float c = 0.0f;
-#pragma unroll
-      for (int j0 = 0; j0 < KP; j0 += 4) {
-        const float4 v4 = *reinterpret_cast<const float4*>(&V[i * KP + j0]);
-        c = __builtin_fmaf(m[j0], v4.x, c);
-        c = __builtin_fmaf(m[j0 + 1], v4.y, c);
-        c = __builtin_fmaf(m[j0 + 2], v4.z, c);
-        c = __builtin_fmaf(m[j0 + 3], v4.w, c);
-      }
-      n2 = __builtin_fmaf(m[i], c, n2);
-    }
-    den = n2;
-  }
-  float sum_obs = 0.0f;
-#pragma unroll
-  for (int i = 0; i < KP; ++i) {
-    float c = 0.0f;
-#pragma unroll
-    for (int j0 = 0; j0 < KP; j0 += 4) {
-      const float4 w4 = *reinterpret_cast<const float4*>(&W[i * KP + j0]);
-      c = __builtin_fmaf(m[j0], w4.x, c);
-      c = __builtin_fmaf(m[j0 + 1], w4.y, c);
-      c = __builtin_fmaf(m[j0 + 2], w4.z, c);
-      c = __builtin_fmaf(m[j0 + 3], w4.w, c);
-    }
-    const float ai = m[i] != 0.0f ? c / den : 0.0f;
-    sum_obs += ai;
-    d[i] = ai;
-  }
-  const float mean = (k >= 2 && rule != PAIR_RULE_MARGINAL) ? sum_obs / (float)k : 0.0f;
-#pragma unroll
-  for (int i = 0; i < KP; ++i) d[i] = valid ? (m[i] != 0.0f ? d[i] - mean : 0.0f) - af[i] : 0.0f;
-
-  if (valid) {
-    float* drow = delta + (b * rrows + rloc) * KP;
-#pragma unroll
-    for (int i0 = 0; i0 < KP; i0 += 4)
-      *reinterpret_cast<float4*>(drow + i0) = make_float4(d[i0], d[i0 + 1], d[i0 + 2], d[i0 + 3]);
-  }
-
-  // Fixed-order column sums: a wave sum (DPP steps within rows of 16 lanes,
-  // then the four rows in order) in each wave, then the waves in order.
-#pragma unroll
-  for (int i = 0; i < KP; ++i) {
-    const float sw = wave_sum(d[i]);
-    if (lane == 0) wsum[wave][i] = sw;
-  }
-  __syncthreads();
-  if (tid < g) {
-    float sc = 0.0f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) sc += wsum[w][tid];
-    dsum[(b * nwg + chunk) * gmax + tid] = sc;
-  }
+  if (bad_rho) raise_status(d_status, PAIR_ST_RHO_RANGE);
 }
 
 // ---------------------------------------------------------------------------
-// 2. delta_bar row and zero padding.
-// ---------------------------------------------------------------------------
-constexpr int kPrepThreads = 256;
-
-// Live prompts: live[0] = their count, live[1 ..] = their indices in
-// ascending order, live[1 + B + b] = 1 if prompt b is live, else 0.  A prompt
-// is live when its group is valid and some reward differs from the first (a
-// NaN reward counts as different).  One workgroup, chunks of 256 prompts, a
-// ballot prefix count within each wave and the waves in order.
-__device__ void list_live_prompts(int64_t B, int64_t nv, int32_t gmax,
-                                  const int64_t* __restrict__ offsets,
-                                  const float* __restrict__ rewards, int32_t* __restrict__ live) {
-  constexpr int kWaves = kPrepThreads / kWave;
-  __shared__ int32_t wcount[kWaves];
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
-  int32_t base = 0;
-  for (int64_t c0 = 0; c0 < B; c0 += kPrepThreads) {
-    const int64_t b = c0 + tid;
-    bool lv = false;
-    if (b < B) {
-      int64_t o0, g;
-      if (prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) {
-        const float r0 = rewards[o0];
-        for (int64_t i = 1; i < g; ++i) lv = lv || !(rewards[o0 + i] == r0);
-      }
-      live[1 + B + b] = lv ? 1 : 0;
-    }
-    const uint64_t m = __ballot(lv);
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
-    if (lane == 0) wcount[wave] = __popcll(m);
-    __syncthreads();
-    int32_t off = base, tot = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      if (w < wave) off += wcount[w];
-      tot += wcount[w];
-    }
-    if (lv) live[1 + off + before] = (int32_t)b;
-    base += tot;
-    __syncthreads();
-  }
-  if (tid == 0) live[0] = base;
-}
-
-__global__ __launch_bounds__(kPrepThreads) void audit_prep_kernel(
-    int64_t B, int64_t nv, int32_t gmax, int kp, const int64_t* __restrict__ offsets,
-    const float* __restrict__ rewards, int64_t R, int64_t rbar, int64_t nwg, int64_t rrows,
-    const float* __restrict__ dsum, float* __restrict__ delta, int32_t* __restrict__ live) {
-  const int64_t b = blockIdx.x;
-  if (b == B) {
-    list_live_prompts(B, nv, gmax, offsets, rewards, live);
-    return;
-  }
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
-  const int tid = threadIdx.x;
-  if (tid < kp) {
-    float v = 0.0f;
-    if (tid < g) {
-      float s = 0.0f;
-      for (int64_t c = 0; c < nwg; ++c) s += dsum[(b * nwg + c) * gmax + tid];
-      v = s / (float)R;
-    }
-    delta[(b * rrows + rbar) * kp + tid] = v;
-  }
-  // Zero rows: R .. rbar-1 (padding of the replicate tiles) and the rest of
-  // the delta_bar tile.
-  const int64_t pad1 = (rbar - R) * kp;
-  float* dst1 = delta + (b * rrows + R) * kp;
-  for (int64_t idx = tid; idx < pad1; idx += blockDim.x) dst1[idx] = 0.0f;
-  const int64_t pad2 = (rrows - rbar - 1) * kp;
-  float* dst2 = delta + (b * rrows + rbar + 1) * kp;
-  for (int64_t idx = tid; idx < pad2; idx += blockDim.x) dst2[idx] = 0.0f;
-}
-
-// ---------------------------------------------------------------------------
-// 3. Matrix-core contraction with the squared-norm epilogue.
+// 3. Replicates: u_i = J_i (1/(2N)) sum_j J_j W_ij (fp32 products and sums),
+//    then in fp64 the division, the centring over the completed vertices (not
+//    for the marginal-only rule, whose fold is not antisymmetric), the target
+//    and the quadratic form.  2N = G (G - 1), or k (k - 1) for the
+//    observed-edge mean, or sum_{i, j observed} 1/rho_ij for the
+//    self-normalised rule.  Fewer than two completed vertices: u = 0.
 //
-// A workgroup owns one prompt and one slice of score columns.  It converts
-// the slice to rescaled fp16 once, keeps it in LDS ([d][i], transposed, one
-// skew row per 8), and then every replicate row of the prompt sweeps over it.
-//
-// v_mfma_f32_32x32x16_f16 (wave64): lane l holds row l % 32 of A and column
-// l % 32 of B, K elements 8*(l/32) .. 8*(l/32)+7 of each 16-wide K step; the
-// 16 accumulators of lane l hold column l % 32 and rows 8*(v/4) + 4*(l/32) +
-// (v%4).  Here A = the S_b slice transposed (rows = score columns d) and
-// B = delta^T (columns = replicates r), so all 16 accumulators of a lane
-// belong to ONE replicate (l % 32): the squared norm is summed inside the
-// lane, and lanes l and l + 32 (the two halves of the d rows) are combined
-// once per tile.  Two accumulator sets alternate between 32-column steps so
-// the matrix instruction of step s issues next to the FMAs squaring step s-1.
+//    Both products are contractions: C = W J^T with v_mfma_f32_16x16x4_f32 and
+//    Y = K x^T with v_mfma_f64_16x16x4_f64, whose rates are those of the
+//    vector units but which need no broadcast of the tables.  Column l % 16 of a result is a replicate; lane l holds vertices
+//    16 ib + 4 (l / 16) + v, v = 0..3, of it in both results, and that is also
+//    the B operand of step 4 ib + v, so C becomes x and x meets Y in place.  One
+//    lane per replicate with the tables in scalar registers took 31 us against
+//    26 us here at B = 256, G = 16, R = 4096, and 123 us against 21 us at B = 64,
+//    G in 2..64, R = 1000, where the 64 x 64 tables exceed the scalar cache.
+//    Bound by the matrix and vector instructions together, which do not
+//    overlap (of 32 us, the fp64 products took 8 and the fp32 ones 4).
 // ---------------------------------------------------------------------------
-template <int KS>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(KS == 1 ? 4 : 2))) void audit_mfma_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t D,
-    const uint16_t* __restrict__ scores, int64_t ld, int64_t rrows, int64_t ntiles,
-    int64_t nslices, const float* __restrict__ delta, const int32_t* __restrict__ live,
-    float* __restrict__ epart, int32_t* d_status) {
-  constexpr int KP = 16 * KS;
-  constexpr int SW = slice_cols(KS);
-  constexpr int kSteps = SW / kTile;
-  constexpr int kRowsLds = SW + SW / 8;
-  constexpr int kPieces = KP * (SW / 8);    // 16-byte pieces of the slice
-  constexpr int kPerThread = (kPieces + kMfmaThreads - 1) / kMfmaThreads;
-  __shared__ __align__(16) uint16_t S_lds[kRowsLds * KP];
-  __shared__ float bar_part[kMfmaWaves];
-  __shared__ float wbar[KP];
-  __shared__ int fbar;
-  __shared__ uint32_t row_max[KP];
-  __shared__ int32_t ex[KP];
-  static_assert(kSteps % 2 == 0 && kSteps >= 4 && SW % kMfmaThreads == 0 && KP <= kWave,
-                "slice shape");
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-  // XCD-aware placement: hardware round-robins workgroup ids over 8 XCDs.
-  // The grid has room for every prompt; the n live (prompt, slice) pairs are
-  // split into 8 contiguous ranges of ceil(n / 8), one per XCD, so the
-  // workgroups of a prompt share that XCD's L2 for the delta rows and the
-  // XCDs get equal work.  Workgroups beyond the live work exit at once.
-  const int64_t n_live = (int64_t)live[0] * nslices;
-  const int64_t per_xcd = (n_live + 7) / 8;
-  const int64_t j = blockIdx.x / 8;
-  if (j >= per_xcd) return;
-  const int64_t L = (int64_t)(blockIdx.x % 8) * per_xcd + j;
-  if (L >= n_live) return;
-  const int64_t b = live[1 + L / nslices];
-  const int64_t sl = L - (L / nslices) * nslices;
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
+// Sum over the four lane groups (rows of 16 lanes), the same in all of them.
+__device__ __forceinline__ double group_sum_d(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  v = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+      __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  lo = __builtin_amdgcn_permlane32_swap((uint32_t)w, (uint32_t)w, false, false);
+  hi = __builtin_amdgcn_permlane32_swap((uint32_t)(w >> 32), (uint32_t)(w >> 32), false, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+         __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
 
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave;
-  const int lane = tid & (kWave - 1);
-  const int64_t col0 = sl * (int64_t)SW;
-  if (tid < KP) row_max[tid] = 0u;
-  __syncthreads();
+// Sums over the 16 lanes of each lane group, the same in all of them.
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp_f<0xB1>(v);
+  v += dpp_f<0x4E>(v);
+  v += dpp_f<0x141>(v);
+  return v + dpp_f<0x140>(v);
+}
 
-  // Stage the slice in two passes.  Pass 1 loads the 16-byte pieces
-  // (piece p -> row i = p % KP, columns d0 .. d0 + 7 with d0 = 8 (p / KP);
-  // columns past D and rows past G read as zero) and finds each row's largest
-  // magnitude within the slice as bf16 bits (integer order = magnitude
-  // order).  Pass 2 rescales row i by 2^-e_i, 2^e_i <= max |s_i| < 2^(e_i+1),
-  // and converts to fp16 with round-to-nearest-even: exact for every value
-  // within 2^17 of that maximum (8 significant bits fit in fp16's normal
-  // range and its subnormals down to 2^-17); smaller values land on fp16's
-  // subnormal grid of 2^-24, an absolute error of at most 2^-25 of the row's
-  // slice maximum.
-  uint4 pv[kPerThread];
-  {
-    const uint16_t* sb = scores + o0 * ld;
-    int cur = -1;
-    uint32_t m = 0;
+__device__ __forceinline__ double row_sum_d(double v) {
+  v += dpp_d<0xB1>(v);
+  v += dpp_d<0x4E>(v);
+  v += dpp_d<0x141>(v);
+  return v + dpp_d<0x140>(v);
+}
+
+// All ones if bit v of a lane's four indicators is set, else 0.
+__device__ __forceinline__ uint32_t vertex_mask(uint32_t nib, int v) {
+  return (uint32_t)__builtin_amdgcn_sbfe((int)nib, v, 1);
+}
+
+__device__ __forceinline__ float masked(float x, uint32_t mask) {
+  return __uint_as_float(__float_as_uint(x) & mask);
+}
+
+// Sum over the four lane groups, the same in all of them.
+__device__ __forceinline__ float group_sum(float v) {
+  auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+// C[ib][cb] = table x J^T for NC blocks of 16 replicates.
+template <int KS, int NC>
+__device__ __forceinline__ void fold_table(const float* table, const uint32_t (&nib)[NC][KS],
+                                           int nb, int lane, f32x4_t (&C)[KS][NC]) {
 #pragma unroll
-    for (int t = 0; t < kPerThread; ++t) {
-      const int pidx = tid + t * kMfmaThreads;
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (pidx < kPieces) {
-        const int i = pidx % KP;
-        const int64_t col = col0 + 8 * (pidx / KP);
-        if (i < g) {
-          const uint16_t* src = sb + (int64_t)i * ld + col;
-          if (col + 8 <= D) {
-            v = load_nt16(src);
-          } else if (col < D) {
-            uint16_t h[8];
+  for (int ib = 0; ib < KS; ++ib)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = (col + e < D) ? src[e] : (uint16_t)0;
-            v.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-            v.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-            v.z = (uint32_t)h[4] | ((uint32_t)h[5] << 16);
-            v.w = (uint32_t)h[6] | ((uint32_t)h[7] << 16);
+    for (int cb = 0; cb < NC; ++cb) C[ib][cb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int jb = 0; jb < KS; ++jb)
+    if (jb < nb) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        float J[NC];   // 1 or 0
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb)
+          J[cb] = __uint_as_float(vertex_mask(nib[cb][jb], s) & 0x3f800000u);
+#pragma unroll
+        for (int ib = 0; ib < KS; ++ib)
+          if (ib < nb) {
+            const float w = table[(ib * (4 * KS) + 4 * jb + s) * kWave + lane];
+#pragma unroll
+            for (int cb = 0; cb < NC; ++cb)
+              C[ib][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, J[cb], C[ib][cb], 0, 0, 0);
           }
-        }
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-        uint32_t mp = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t lo = w4[k] & 0x7fffu, hi = (w4[k] >> 16) & 0x7fffu;
-          mp = lo > mp ? lo : mp;
-          mp = hi > mp ? hi : mp;
-        }
-        if (i != cur) {
-          if (cur >= 0 && m != 0u) atomicMax(&row_max[cur], m);
-          cur = i;
-          m = 0;
-        }
-        m = mp > m ? mp : m;
-      }
-      pv[t] = v;
-    }
-    if (cur >= 0 && m != 0u) atomicMax(&row_max[cur], m);
-  }
-  __syncthreads();
-  // Per-row exponents, and the delta_bar row rescaled like a replicate row:
-  // w_i = delta_bar_i 2^(e_i - f) with f putting the largest entry in [1, 2).
-  // The first wave holds all KP rows; its shuffles run on every lane.
-  const float* dbar = delta + (b * rrows + (ntiles - 1) * kTile) * KP;
-  if (wave == 0) {
-    float y = 0.0f;
-    if (lane < KP) {
-      const uint32_t mm = row_max[lane];
-      int32_t e = 0;
-      if (mm >= 0x7f80u) {               // inf or NaN in the row
-        raise_status(d_status, PAIR_ST_NONFINITE);
-      } else if (mm != 0u) {
-        e = (int32_t)(mm >> 7) - 127;    // -127 for a row of subnormals
-      }
-      ex[lane] = e;
-      y = ldexpf(dbar[lane], e);
-    }
-    float m = fabsf(y);
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
-    const int f = m > 0.0f ? ilogbf(m) : 0;
-    if (lane < KP) wbar[lane] = ldexpf(y, -f);
-    if (lane == 0) fbar = f;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kPerThread; ++t) {
-    const int pidx = tid + t * kMfmaThreads;
-    if (pidx < kPieces) {
-      const int i = pidx % KP;
-      const int d0 = 8 * (pidx / KP);
-      const int ne = -ex[i];
-      const uint32_t w4[4] = {pv[t].x, pv[t].y, pv[t].z, pv[t].w};
-      uint16_t* dst = &S_lds[(d0 + d0 / 8) * KP + i];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float lo = ldexpf(bf16lo_to_f32(w4[k]), ne), hi = ldexpf(bf16hi_to_f32(w4[k]), ne);
-        dst[(2 * k) * KP] = __builtin_bit_cast(uint16_t, (_Float16)lo);
-        dst[(2 * k + 1) * KP] = __builtin_bit_cast(uint16_t, (_Float16)hi);
       }
     }
-  }
-  __syncthreads();
-
-  // A fragment (score columns) of step s: lane l reads column 32 s + l % 32 and
-  // the 8 rows 8 (l / 32) .. +7 of every 16-row K step.
-  const int dl = lane & 31;
-  const int aoff = (dl + dl / 8) * KP + 8 * (lane >> 5);
-  auto read_a = [&](int step, f16x8_t (&Af)[KS]) {
-    const uint16_t* src = &S_lds[step * (kTile + kTile / 8) * KP + aoff];
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-      Af[s] = __builtin_bit_cast(f16x8_t, *reinterpret_cast<const uint4*>(src + 16 * s));
-  };
-  // B fragment (replicate rows) of tile t: lane l holds replicate row
-  // 32 t + l % 32, K entries 16 s + 8 (l / 32) + j, rescaled by 2^(e_i - f_r)
-  // with f_r putting the row's largest entry in [1, 2).
-  auto load_b = [&](int64_t t, f16x8_t (&Bf)[KS], int& f) {
-    const int kh = 8 * (lane >> 5);
-    const float* src = delta + (b * rrows + t * kTile + dl) * KP + kh;
-    float y[KS][8];
-    float m = 0.0f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const float4 u0 = *reinterpret_cast<const float4*>(src + 16 * s);
-      const float4 u1 = *reinterpret_cast<const float4*>(src + 16 * s + 4);
-      const float x[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        y[s][j] = ldexpf(x[j], ex[16 * s + kh + j]);
-        m = fmaxf(m, fabsf(y[s][j]));
-      }
-    }
-    m = fmaxf(m, __shfl_xor(m, 32, kWave));   // the row's other K half
-    f = m > 0.0f ? ilogbf(m) : 0;
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) Bf[s][j] = (_Float16)ldexpf(y[s][j], -f);
-  };
-
-  // Sweep a pair of tiles over all steps of the slice; returns each tile's
-  // sum of squares for replicate row l % 32 (lanes l and l + 32 combined).
-  auto sweep = [&](const f16x8_t (&Bt)[kPair][KS], float (&out)[kPair]) {
-    f32x16_t accA[kPair], accB[kPair];
-    float sq[kPair][4];
-#pragma unroll
-    for (int q = 0; q < kPair; ++q)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) sq[q][k] = 0.0f;
-    auto first = [&](const f16x8_t (&Af)[KS], f32x16_t (&acc)[kPair]) {
-#pragma unroll
-      for (int q = 0; q < kPair; ++q) {
-        f32x16_t a;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) a[v] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-          a = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[q][s], a, 0, 0, 0);
-        acc[q] = a;
-      }
-    };
-    auto step = [&](const f16x8_t (&Af)[KS], f32x16_t (&acc)[kPair], const f32x16_t (&prev)[kPair]) {
-#pragma unroll
-      for (int q = 0; q < kPair; ++q) {
-        f32x16_t a;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) a[v] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-          a = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[q][s], a, 0, 0, 0);
-        acc[q] = a;
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          sq[q][v & 3] = __builtin_fmaf(prev[q][v], prev[q][v], sq[q][v & 3]);
-        __builtin_amdgcn_sched_group_barrier(0x008, KS, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    // Step 0 has no previous step to square; steps 1 .. kSteps-1 each square
-    // the one before, and the last is squared after the loop.
-    f16x8_t A0[KS], A1[KS];
-    read_a(0, A0);
-    read_a(1, A1);
-    first(A0, accA);
-    read_a(2, A0);
-    step(A1, accB, accA);
-    for (int st = 2; st < kSteps; st += 2) {
-      read_a(st + 1, A1);
-      step(A0, accA, accB);
-      if (st + 2 < kSteps) read_a(st + 2, A0);
-      step(A1, accB, accA);
-    }
-#pragma unroll
-    for (int q = 0; q < kPair; ++q) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sq[q][v & 3] = __builtin_fmaf(accB[q][v], accB[q][v], sq[q][v & 3]);
-      float tot = (sq[q][0] + sq[q][1]) + (sq[q][2] + sq[q][3]);
-      tot += __shfl_xor(tot, 32, kWave);
-      out[q] = tot;
-    }
-  };
-
-  // The delta_bar row on the vector units: one dot product per score column
-  // of the slice (KP FMAs against the fp16 slice in LDS), squares summed per
-  // thread, then over the wave and the waves in a fixed order.  It is one row
-  // against the slice's 2 x (R rounded up to 64) replicate-row sweeps.
-  {
-    float bsq = 0.0f;
-    for (int c = tid; c < SW; c += kMfmaThreads) {
-      const int cl = c % kTile;
-      const uint16_t* src = &S_lds[(c / kTile) * (kTile + kTile / 8) * KP + (cl + cl / 8) * KP];
-      float y = 0.0f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const uint4 h0 = *reinterpret_cast<const uint4*>(src + 16 * s);
-        const uint4 h1 = *reinterpret_cast<const uint4*>(src + 16 * s + 8);
-        const uint32_t hw[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float lo = (float)__builtin_bit_cast(_Float16, (uint16_t)(hw[j] & 0xffffu));
-          const float hi = (float)__builtin_bit_cast(_Float16, (uint16_t)(hw[j] >> 16));
-          y = __builtin_fmaf(wbar[16 * s + 2 * j], lo, y);
-          y = __builtin_fmaf(wbar[16 * s + 2 * j + 1], hi, y);
-        }
-      }
-      bsq = __builtin_fmaf(y, y, bsq);
-    }
-#pragma unroll
-    for (int o = kWave / 2; o >= 1; o >>= 1) bsq += __shfl_xor(bsq, o, kWave);
-    if (lane == 0) bar_part[wave] = bsq;
-  }
-
-  float* eo = epart + (b * nslices + sl) * rrows;
-  // Replicate tiles (an even count) in pairs, round-robin over the waves, so
-  // every replicate's partial is formed the same way whatever R and the first
-  // replicate index.
-  const int64_t per_round = (int64_t)kPair * kMfmaWaves;
-  const int64_t nmain = ntiles - 1;
-  for (int64_t t0 = (int64_t)wave * kPair; t0 < nmain; t0 += per_round) {
-    f16x8_t Bt[kPair][KS];
-    int fr[kPair];
-#pragma unroll
-    for (int q = 0; q < kPair; ++q) load_b(t0 + q, Bt[q], fr[q]);
-    float out[kPair];
-    sweep(Bt, out);
-    if (lane < kTile) {
-#pragma unroll
-      for (int q = 0; q < kPair; ++q) eo[(t0 + q) * kTile + lane] = ldexpf(out[q], 2 * fr[q]);
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float tot = 0.0f;
-    for (int w = 0; w < kMfmaWaves; ++w) tot += bar_part[w];
-    eo[nmain * kTile] = ldexpf(tot, 2 * fbar);
-  }
 }
 
-// ---------------------------------------------------------------------------
-// 4. Fixed-order reductions.  audit_sqerr: one thread per (prompt, replicate
-//    row) sums the per-slice partials in slice order (fp32) into e_r, and
-//    each workgroup writes the fp64 sum of its e_r; audit_final: per prompt,
-//    MSE = (sum of those partials in order) / R and bias = sqrt(e of delta_bar).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSqThreads) void audit_sqerr_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t R,
-    int64_t rbar, int64_t rrows, int64_t nslices, int64_t nsq, const float* __restrict__ epart,
-    const int32_t* __restrict__ live, double* __restrict__ rpart, float* __restrict__ ebar,
-    float* __restrict__ rep_sqerr) {
-  __shared__ double part[kSqThreads / kWave];
-  const int64_t b = blockIdx.x / nsq;
-  const int64_t c = blockIdx.x - b * nsq;
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
-  const int64_t r = c * kSqThreads + threadIdx.x;
-  const bool is_live = live[1 + B + b] != 0;   // not live: every delta_r is 0, so e_r = 0
-  float e = 0.0f;
-  if (r <= R && is_live) {
-    const float* eb = epart + b * nslices * rrows + (r < R ? r : rbar);
-    int64_t k = 0;
-    for (; k + 8 <= nslices; k += 8) {
-      float v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = eb[(k + q) * rrows];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) e += v[q];
-    }
-    for (; k < nslices; ++k) e += eb[k * rrows];
-  }
-  if (r < R && rep_sqerr != nullptr) rep_sqerr[b * R + r] = e;
-  if (r == R) ebar[b] = e;
-  double s = r < R ? (double)e : 0.0;
-#pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) s += __shfl_xor(s, m, kWave);
-  const int wave = threadIdx.x / kWave;
-  if ((threadIdx.x & (kWave - 1)) == 0) part[wave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int w = 0; w < kSqThreads / kWave; ++w) t += part[w];
-    rpart[b * nsq + c] = t;
-  }
-}
-
-__global__ __launch_bounds__(256) void audit_final_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t R,
-    int64_t nsq, const double* __restrict__ rpart, const float* __restrict__ ebar,
-    double* __restrict__ mse, double* __restrict__ bias_norm) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
-  double t = 0.0;
-  for (int64_t c = 0; c < nsq; ++c) t += rpart[b * nsq + c];
-  mse[b] = t / (double)R;
-  bias_norm[b] = sqrt((double)ebar[b]);
-}
-
-// ---------------------------------------------------------------------------
-// Update direction (Sec. 6.2 audit metrics; the Cosine column of the audit
-// matrix, App. E).  Replicate r's estimate is g_r = u_r S_b with
-// u_r = delta_r + a (its fold's coefficients) and the target is t = a S_b, so
-// with the fp64 Gram matrix K = S_b S_b^T
-//     cos_r = u_r K a / sqrt(u_r K u_r * a K a),
-// taken as 0 when either quadratic form is not positive (a draw with no
-// observed edge has u_r = 0 exactly; a prompt with equal rewards has a = 0).
-// A workgroup owns one prompt and 256 replicates (one per thread) and writes
-// the fixed-order sum of its cosines; a second kernel adds the chunks in
-// order.  a is recomputed exactly as audit_coeffs_kernel computes it, so
-// delta_r + a restores the fold's coefficients to within one fp32 rounding.
-// ---------------------------------------------------------------------------
-constexpr int kCosThreads = 256;
-
-template <int KP>
-__global__ __launch_bounds__(kCosThreads) void audit_cosine_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
-    const float* __restrict__ rewards, int64_t R, int64_t nwg, int64_t rrows,
-    const float* __restrict__ delta, const double* __restrict__ gram, double* __restrict__ cpart,
-    double* __restrict__ target_norm) {
-  constexpr int kWaves = kCosThreads / kWave;
-  __shared__ double K[KP * KP];
-  __shared__ double ka[KP];
-  __shared__ float af[KP];
+template <int KS, bool COS>
+__global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
+    int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int32_t rule, int64_t R,
+    int64_t nchunk, int rounds, const double* __restrict__ K, const float* __restrict__ wt,
+    const float* __restrict__ vt, const double* __restrict__ a_full,
+    const int32_t* __restrict__ flag, const uint64_t* __restrict__ bits,
+    double* __restrict__ epart, float* __restrict__ dpart, float* __restrict__ rep_sqerr,
+    int32_t* __restrict__ edge_count, double* __restrict__ target_norm) {
+  constexpr int KP = 16 * KS;
+  constexpr int NC = KS <= 2 ? 4 : 2;   // blocks of 16 replicates at once
+  constexpr int kWaves = kEvalThreads / kWave;
+  __shared__ __align__(16) double Ks[KP * KP];
+  __shared__ __align__(16) float Ws[KP * KP];
+  __shared__ float wsum[kWaves][KP];
   __shared__ double red[kWaves];
-  __shared__ double tt_s;
-  const int64_t b = blockIdx.x / nwg;
-  const int64_t chunk = blockIdx.x - b * nwg;
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
+  __shared__ double recip[PAIR_GMAX_LIMIT + 1];
+  __shared__ float recip32[PAIR_GMAX_LIMIT + 1];
+  const int64_t b = blockIdx.x / nchunk;
+  const int64_t chunk = blockIdx.x - b * nchunk;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int grp = lane >> 4;
+  const int64_t first = (chunk * kWaves + wave) * rounds * kWave;   // this wave's replicates
+  // Everything that depends on the prompt's number alone is asked for before
+  // its size is known: one memory latency instead of four in a row.
+  uint64_t next[NC];
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      const int64_t r = first + (int64_t)t * (16 * NC) + 16 * cb + (lane & 15);
+      next[cb] = r < R ? bits[b * R + r] : 0ull;
+    }
+  };
+  fetch(0);
+  double af[KS][4];
+#pragma unroll
+  for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) af[ib][v] = a_full[b * KP + 16 * ib + 4 * grp + v];
+  const double* Kb = K + b * (KP * KP);
+  for (int idx = 2 * tid; idx < KP * KP; idx += 2 * kEvalThreads)
+    *reinterpret_cast<double2*>(Ks + idx) = *reinterpret_cast<const double2*>(Kb + idx);
+  for (int idx = 4 * tid; idx < KP * KP; idx += 4 * kEvalThreads)
+    *reinterpret_cast<float4*>(Ws + idx) =
+        *reinterpret_cast<const float4*>(wt + b * (KP * KP) + idx);
+  const bool live = COS || flag[b] != 0;
   int64_t o0, g64;
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
   const int g = (int)g64;
-
-  if (wave == 0) {
-    const float r_i = lane < g ? rewards[o0 + lane] : 0.0f;
-    const float a_full = complete_pair_coeff(r_i, lane, g);
-    if (lane < KP) af[lane] = a_full;
+  const int nb = KS == 1 ? 1 : (g + 15) / 16;
+  const uint64_t group = g == 64 ? ~0ull : (1ull << g) - 1ull;   // bits the draws wrote
+  if (!live) {   // equal rewards: every delta_r is exactly 0
+    for (int t = 0; t < rounds; ++t) {
+      const int64_t r = first + t * kWave + lane;
+      if (r >= R) break;
+      if (rep_sqerr != nullptr) rep_sqerr[b * R + r] = 0.0f;
+      if (edge_count != nullptr) {
+        const int k = __popcll(bits[b * R + r] & group);
+        edge_count[b * R + r] = k * (k - 1) / 2;
+      }
+    }
+    return;   // audit_final looks at the flag too
   }
-  for (int idx = tid; idx < KP * KP; idx += kCosThreads) {
-    const int i = idx / KP, j = idx - i * KP;
-    K[idx] = (i < g && j < g) ? gram[(b * gmax + i) * (int64_t)gmax + j] : 0.0;
+  if (tid <= PAIR_GMAX_LIMIT) {
+    recip[tid] = tid > 0 ? 1.0 / (double)tid : 0.0;
+    recip32[tid] = rule != PAIR_RULE_MARGINAL ? (float)recip[tid] : 0.0f;   // not centred
   }
   __syncthreads();
-  if (tid < KP) {
-    double v = 0.0;
-    for (int j = 0; j < g; ++j) v += K[tid * KP + j] * (double)af[j];
-    ka[tid] = v;
+  const double inv_pool = 1.0 / (double)(g * (g - 1));
+
+  // x K x^T of the columns: off the diagonal blocks each pair of blocks counts
+  // twice.
+  auto quadratic = [&](const auto& x, auto& q) {
+    constexpr int N = sizeof(q) / sizeof(q[0]);
+#pragma unroll
+    for (int cb = 0; cb < N; ++cb) q[cb] = 0.0;
+#pragma unroll
+    for (int ib = 0; ib < KS; ++ib)
+      if (ib < nb) {
+        f64x4_t Y[N], D[N];
+#pragma unroll
+        for (int cb = 0; cb < N; ++cb) Y[cb] = D[cb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int jb = ib; jb < KS; ++jb)
+          if (jb < nb) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              const double kf = Ks[(ib * (4 * KS) + 4 * jb + s) * kWave + lane];
+#pragma unroll
+              for (int cb = 0; cb < N; ++cb) {
+                if (jb == ib)
+                  D[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kf, x[jb][cb][s], D[cb], 0, 0, 0);
+                else
+                  Y[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kf, x[jb][cb][s], Y[cb], 0, 0, 0);
+              }
+            }
+          }
+#pragma unroll
+        for (int cb = 0; cb < N; ++cb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double y = KS == 1 ? D[cb][v] : __builtin_fma(2.0, Y[cb][v], D[cb][v]);
+            q[cb] = __builtin_fma(x[ib][cb][v], y, q[cb]);
+          }
+      }
+  };
+
+  // For the cosine: af becomes K a, and tt = a K a.
+  double tt = 0.0;
+  if (COS) {
+    f64x4_t Y[KS];
+#pragma unroll
+    for (int ib = 0; ib < KS; ++ib) {
+      Y[ib] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+      if (ib < nb) {
+#pragma unroll
+        for (int jb = 0; jb < KS; ++jb)
+          if (jb < nb) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+              Y[ib] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                  Ks[(ib * (4 * KS) + 4 * jb + s) * kWave + lane], af[jb][s], Y[ib], 0, 0, 0);
+          }
+      }
+    }
+#pragma unroll
+    for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        tt = __builtin_fma(af[ib][v], Y[ib][v], tt);
+        af[ib][v] = Y[ib][v];
+      }
+    tt = group_sum_d(tt);
+    if (chunk == 0 && tid == 0) target_norm[b] = tt > 0.0 ? sqrt(tt) : 0.0;
+  }
+
+  // Sums of the centred folds, times the normaliser where it varies.
+  // (Factors instead of branches: the blocks of replicates stay one basic block,
+  // whose chains interleave.)
+  const float varies = (rule == PAIR_RULE_RATIO_KE || rule == PAIR_RULE_SELFNORM) ? 1.0f : 0.0f;
+  float csum[KS][4];
+#pragma unroll
+  for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) csum[ib][v] = 0.0f;
+  double esum = 0.0;
+  const int steps = rounds * (4 / NC);
+#pragma unroll 1
+  for (int t = 0; t < steps; ++t) {
+    const int64_t r0 = first + (int64_t)t * (16 * NC) + (lane & 15);
+    uint32_t nib[NC][KS];   // this lane's four indicators of each block of vertices
+    int k[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      const uint64_t drawn = next[cb] & group;
+      k[cb] = __popcll(drawn);
+      const uint64_t word = k[cb] < 2 ? 0ull : drawn;
+#pragma unroll
+      for (int ib = 0; ib < KS; ++ib)
+        nib[cb][ib] = (uint32_t)(word >> (32 * (ib / 2))) >> (16 * (ib % 2) + 4 * grp);
+    }
+    if (t + 1 < steps) fetch(t + 1);
+    f32x4_t C[KS][NC];
+    double inv[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) inv[cb] = inv_pool;
+    if (rule == PAIR_RULE_RATIO_KE) {
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+        inv[cb] = k[cb] >= 2 ? recip[k[cb]] * recip[k[cb] - 1] : 0.0;
+    } else if (rule == PAIR_RULE_SELFNORM) {
+      fold_table<KS, NC>(vt + b * (KP * KP), nib, nb, lane, C);
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        double n2 = 0.0;
+#pragma unroll
+        for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            n2 += (double)masked(C[ib][cb][v], vertex_mask(nib[cb][ib], v));
+        n2 = group_sum_d(n2);
+        inv[cb] = k[cb] >= 2 ? 1.0 / n2 : 0.0;
+      }
+    }
+    fold_table<KS, NC>(Ws, nib, nb, lane, C);
+
+    // The folds c_i = sum_j J_j W_ij of the completed vertices are centred in
+    // fp32; the normaliser, whose rounding would be the same in every
+    // replicate and so survive in their mean, is applied in fp64.
+    double x[KS][NC][4];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      float sum = 0.0f;
+#pragma unroll
+      for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          C[ib][cb][v] = masked(C[ib][cb][v], vertex_mask(nib[cb][ib], v));
+          sum += C[ib][cb][v];
+        }
+      const float mean = group_sum(sum) * recip32[k[cb]];
+      const float weight = __builtin_fmaf(varies, (float)inv[cb], 1.0f - varies);
+#pragma unroll
+      for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float c = masked(C[ib][cb][v] - mean, vertex_mask(nib[cb][ib], v));
+          if (COS) {
+            x[ib][cb][v] = (double)c * inv[cb];
+          } else {
+            x[ib][cb][v] = __builtin_fma((double)c, inv[cb], -af[ib][v]);
+            csum[ib][v] = __builtin_fmaf(c, weight, csum[ib][v]);
+          }
+        }
+    }
+
+    double q[NC];
+    quadratic(x, q);
+
+    double mine = 0.0;   // the replicate this lane stores: block grp
+    int my_k = 0;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      double e = group_sum_d(q[cb]);
+      if (COS) {
+        double uka = 0.0;
+#pragma unroll
+        for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) uka = __builtin_fma(x[ib][cb][v], af[ib][v], uka);
+        uka = group_sum_d(uka);
+        // 0 when either quadratic form is not positive (a draw with no observed
+        // edge has u_r = 0 exactly; a prompt with equal rewards has a = 0).
+        e = (r0 + 16 * cb < R && tt > 0.0 && e > 0.0) ? uka / sqrt(e * tt) : 0.0;
+      } else {
+        // rounding: the form is not negative; replicates past R count nothing
+        e = (e < 0.0 || r0 + 16 * cb >= R) ? 0.0 : e;
+      }
+      if (grp == cb) {
+        mine = e;
+        my_k = k[cb];
+      }
+      esum += e;
+    }
+    if (!COS) {
+      const int64_t r = r0 + 16 * grp;
+      if (grp < NC && r < R) {
+        if (rep_sqerr != nullptr) rep_sqerr[b * R + r] = (float)mine;
+        if (edge_count != nullptr) edge_count[b * R + r] = my_k * (my_k - 1) / 2;
+      }
+    }
+  }
+
+  // Fixed-order sums over the replicates: the 16 columns, then the waves in order.
+  esum = row_sum_d(esum);
+  if (lane == 0) red[wave] = esum;
+  if (!COS) {
+#pragma unroll
+    for (int ib = 0; ib < KS; ++ib)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float s = row_sum(csum[ib][v]);
+        if ((lane & 15) == 0) wsum[wave][16 * ib + 4 * grp + v] = s;
+      }
   }
   __syncthreads();
   if (tid == 0) {
-    double t2 = 0.0;
-    for (int i = 0; i < g; ++i) t2 += (double)af[i] * ka[i];
-    tt_s = t2;
-    if (chunk == 0) target_norm[b] = t2 > 0.0 ? sqrt(t2) : 0.0;
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t += red[w];
+    epart[b * nchunk + chunk] = t;
   }
-  __syncthreads();
-  const double tt = tt_s;
-
-  const int64_t rloc = chunk * kCosThreads + tid;
-  double cosv = 0.0;
-  if (rloc < R && tt > 0.0) {
-    const float* drow = delta + (b * rrows + rloc) * KP;
-    double u[KP];
+  if (!COS && tid < KP) {
+    float s = 0.0f;
 #pragma unroll
-    for (int i0 = 0; i0 < KP; i0 += 4) {
-      const float4 v4 = *reinterpret_cast<const float4*>(drow + i0);
-      u[i0] = (double)(v4.x + af[i0]);
-      u[i0 + 1] = (double)(v4.y + af[i0 + 1]);
-      u[i0 + 2] = (double)(v4.z + af[i0 + 2]);
-      u[i0 + 3] = (double)(v4.w + af[i0 + 3]);
-    }
-    double uka = 0.0, uku = 0.0;
-    for (int i = 0; i < g; ++i) {
-      double ki = 0.0;
-#pragma unroll
-      for (int j = 0; j < KP; ++j) ki += K[i * KP + j] * u[j];
-      double ui = 0.0;
-#pragma unroll
-      for (int q = 0; q < KP; ++q) ui = q == i ? u[q] : ui;
-      uku += ui * ki;
-      uka += ui * ka[i];
-    }
-    if (uku > 0.0) cosv = uka / sqrt(uku * tt);
-  }
-  // Fixed-order sum: butterfly within each wave, then the waves in order.
-#pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) cosv += __shfl_xor(cosv, m, kWave);
-  if (lane == 0) red[wave] = cosv;
-  __syncthreads();
-  if (tid == 0) {
-    double sum = 0.0;
-    for (int w = 0; w < kWaves; ++w) sum += red[w];
-    cpart[b * nwg + chunk] = sum;
+    for (int w = 0; w < kWaves; ++w) s += wsum[w][tid];
+    dpart[(b * nchunk + chunk) * KP + tid] = s;
   }
 }
 
-__global__ __launch_bounds__(256) void audit_cosine_final_kernel(
-    int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t R,
-    int64_t nwg, const double* __restrict__ cpart, double* __restrict__ cosine) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  int64_t o0, g;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
-  double sum = 0.0;
-  for (int64_t c = 0; c < nwg; ++c) sum += cpart[b * nwg + c];
-  cosine[b] = sum / (double)R;
+// ---------------------------------------------------------------------------
+// 4. Fixed-order reductions over the replicate chunks, one wave per prompt.
+// ---------------------------------------------------------------------------
+template <bool COS>
+__global__ __launch_bounds__(kWave) void audit_final_kernel(
+    int64_t nv, int32_t gmax, int kp, const int64_t* __restrict__ offsets, int32_t rule, int64_t R,
+    int64_t nchunk, const double* __restrict__ K, const double* __restrict__ a_full,
+    const int32_t* __restrict__ flag,
+    const double* __restrict__ epart, const float* __restrict__ dpart, double* __restrict__ first,
+    double* __restrict__ bias_norm) {
+  const int64_t b = blockIdx.x;
+  const int lane = threadIdx.x;
+  int64_t o0, g64;
+  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
+  const int g = (int)g64;
+  if (!COS && flag[b] == 0) {   // equal rewards: exact zeros
+    if (lane == 0) {
+      first[b] = 0.0;
+      bias_norm[b] = 0.0;
+    }
+    return;
+  }
+  double t = 0.0;
+  for (int64_t c = lane; c < nchunk; c += kWave) t += epart[b * nchunk + c];
+  t = wave_sum_d(t);
+  if (lane == 0) first[b] = t / (double)R;   // the MSE, or the mean cosine
+  if (COS) return;
+  double d = 0.0;
+  if (lane < g) {
+    int64_t c = 0;
+    for (; c + 8 <= nchunk; c += 8) {   // eight loads in flight
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = dpart[(b * nchunk + c + q) * kp + lane];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) d += (double)v[q];
+    }
+    for (; c < nchunk; ++c) d += (double)dpart[(b * nchunk + c) * kp + lane];
+    // mean of u, less the target's coefficients
+    const bool uniform = rule != PAIR_RULE_RATIO_KE && rule != PAIR_RULE_SELFNORM;
+    d = d / ((double)R * (uniform ? (double)(g * (g - 1)) : 1.0)) - a_full[b * kp + lane];
+  }
+  double y = 0.0;
+  for (int j0 = 0; j0 < g; j0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q)   // lanes past the group read row 0
+      v[q] = K[b * (kp * kp) + frag_place64(kp, lane < g ? lane : 0, j0 + q)];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) y = __builtin_fma(v[q], readlane_d(d, j0 + q), y);
+  }
+  const double q = wave_sum_d(d * y);   // d is 0 past the group
+  if (lane == 0) bias_norm[b] = q > 0.0 ? sqrt(q) : (q == q ? 0.0 : q);
+}
+
+struct AuditArgs {
+  int64_t B, nv;
+  int32_t gmax;
+  const int64_t* offsets;
+  int64_t D;
+  const void* scores;
+  int64_t ld;
+  const float *rewards, *p, *pi_w;
+  int32_t rule;
+  float wmax;
+  uint64_t seed;
+  int64_t rep0, pbase, R;
+  double *first, *second;   // mse and bias norm, or cosine and target norm
+  float* rep_sqerr;
+  int32_t* edge_count;
+  void* workspace;
+  int32_t* d_status;
+  hipStream_t stream;
+};
+
+template <int KS, bool COS>
+int run_audit(const AuditLayout& L, const AuditArgs& A) {
+  unsigned char* ws = static_cast<unsigned char*>(A.workspace);
+  float* part = reinterpret_cast<float*>(ws + L.part_off);
+  int32_t* gex = reinterpret_cast<int32_t*>(ws + L.gex_off);
+  double* K = reinterpret_cast<double*>(ws + L.k_off);
+  float* wt = reinterpret_cast<float*>(ws + L.w_off);
+  float* vt = reinterpret_cast<float*>(ws + L.v_off);
+  double* a = reinterpret_cast<double*>(ws + L.a_off);
+  int32_t* flag = reinterpret_cast<int32_t*>(ws + L.flag_off);
+  uint64_t* bits = reinterpret_cast<uint64_t*>(ws + L.bits_off);
+  double* epart = reinterpret_cast<double*>(ws + L.epart_off);
+  float* dpart = reinterpret_cast<float*>(ws + L.dpart_off);
+  const uint16_t* s = static_cast<const uint16_t*>(A.scores);
+
+  // Every grid size is checked before the first launch.
+  const int64_t stream_grid = A.B * L.slots, eval_grid = A.B * L.nchunk;
+  const int64_t table_grid = A.B * (gram_tiles(KS) + 1);
+  if (stream_grid > 0x7fffffffLL || eval_grid > 0x7fffffffLL || table_grid > 0x7fffffffLL)
+    return PAIR_ERANGE;
+  // The cosine audit reports what its Gram matrix holds, so it reads every
+  // prompt and leaves the products unscaled: an overflow is a non-finite entry.
+  const int own = COS ? 0 : 1;
+  hipLaunchKernelGGL((audit_stream_kernel<KS>), dim3((unsigned)stream_grid), dim3(kGramThreads), 0,
+                     A.stream, A.nv, A.gmax, A.offsets, A.D, s, A.ld, (int)L.nsl, L.slice,
+                     (int)L.slots, A.rewards, A.p, A.seed, A.rep0, A.pbase, A.R, own, own, part, gex,
+                     reinterpret_cast<uint16_t*>(bits), A.edge_count != nullptr ? 1 : 0,
+                     A.d_status);
+  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
+  hipLaunchKernelGGL((audit_tables_kernel<KS>), dim3((unsigned)table_grid), dim3(kTableThreads), 0,
+                     A.stream, A.nv, A.gmax, A.offsets, A.rewards, A.p, A.pi_w, A.rule, A.wmax,
+                     L.nsl, own, part, gex, K, wt, vt, a, flag, A.d_status);
+  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
+  hipLaunchKernelGGL((audit_eval_kernel<KS, COS>), dim3((unsigned)eval_grid), dim3(kEvalThreads), 0,
+                     A.stream, A.nv, A.gmax, A.offsets, A.rule, A.R, L.nchunk, L.rounds, K, wt, vt,
+                     a, flag, bits, epart, dpart, A.rep_sqerr, A.edge_count,
+                     COS ? A.second : nullptr);
+  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
+  hipLaunchKernelGGL((audit_final_kernel<COS>), dim3((unsigned)A.B), dim3(kWave), 0, A.stream, A.nv,
+                     A.gmax, L.kp, A.offsets, A.rule, A.R, L.nchunk, K, a, flag, epart, dpart, A.first,
+                     A.second);
+  return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
+}
+
+template <bool COS>
+int launch_any(const AuditArgs& A) {
+  const AuditLayout L = audit_layout(A.B, A.gmax, A.D, A.R);
+  switch (L.ks) {
+    case 1: return run_audit<1, COS>(L, A);
+    case 2: return run_audit<2, COS>(L, A);
+    case 3: return run_audit<3, COS>(L, A);
+    default: return run_audit<4, COS>(L, A);
+  }
 }
 
 }  // namespace
 
-size_t audit_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R) {
-  return audit_layout(B, gmax, D, R).total;
+// The size a caller is asked for.  It is the one of the column-by-column
+// contraction (fp32 deviations of every replicate and their per-slice sums),
+// so that buffers sized by it, and the calls that pair_audit_noalloc's fixed
+// scratch admits, stay what they were; what the audit writes (audit_need_bytes) is
+// less except for a few replicates of wide groups, where it decides.
+static size_t contraction_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R, bool direction) {
+  const int64_t ks = (gmax + 15) / 16, kp = 16 * ks;
+  const int64_t rrows = round_up(R, 64) + 32, nwg = ceil_div(R, 256);
+  const int64_t cols = ks == 1 ? 2048 : (ks == 2 ? 1024 : 512);
+  size_t n = (size_t)round_up(B * rrows * kp * 4, 256) + (size_t)round_up(B * nwg * gmax * 4, 256);
+  if (direction)
+    return n + (size_t)round_up((int64_t)exact_workspace_bytes(B, gmax, D), 256) +
+           (size_t)round_up(B * (int64_t)gmax * gmax * 8, 256) + (size_t)round_up(B * nwg * 8, 256);
+  return n + (size_t)round_up(B * ceil_div(D, cols) * rrows * 4, 256) +
+         (size_t)round_up(B * ceil_div(R + 1, 256) * 8, 256) + (size_t)round_up(B * 4, 256) +
+         (size_t)round_up((2 * B + 1) * 4, 256);
 }
 
-// Workspace of launch_audit_direction: the Gram slice partials, the fp64
-// Gram matrices, the replicate deviations and their partial sums (as in the
-// audit), and the per-chunk cosine sums.
-struct DirectionLayout {
-  size_t gram_part_off, gram_off, delta_off, dsum_off, cpart_off, total;
-};
+size_t audit_need_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R) {
+  return audit_layout(B, gmax, D, R).need;
+}
 
-DirectionLayout direction_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
-  const AuditLayout A = audit_layout(B, gmax, D, R);
-  DirectionLayout L;
-  size_t off = 0;
-  L.gram_part_off = off;
-  off += (size_t)round_up((int64_t)exact_workspace_bytes(B, gmax, D), 256);
-  L.gram_off = off;
-  off += (size_t)round_up(B * (int64_t)gmax * gmax * 8, 256);
-  L.delta_off = off;
-  off += (size_t)round_up(B * A.rrows * A.kp * 4, 256);
-  L.dsum_off = off;
-  off += (size_t)round_up(B * A.nwg * gmax * 4, 256);
-  L.cpart_off = off;
-  off += (size_t)round_up(B * A.nwg * 8, 256);
-  L.total = off;
-  return L;
+size_t audit_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R) {
+  const size_t a = contraction_bytes(B, gmax, D, R, false), n = audit_need_bytes(B, gmax, D, R);
+  return a > n ? a : n;
 }
 
 size_t direction_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R) {
-  return direction_layout(B, gmax, D, R).total;
+  const size_t a = contraction_bytes(B, gmax, D, R, true), n = audit_need_bytes(B, gmax, D, R);
+  return a > n ? a : n;
 }
 
 int launch_audit_direction(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, int64_t D,
@@ -899,38 +881,9 @@ int launch_audit_direction(int64_t B, int64_t nv, int32_t gmax, const int64_t* o
                            const float* pi_w, int32_t rule, float wmax, uint64_t seed,
                            int64_t rep0, int64_t R, double* cosine, double* target_norm,
                            void* workspace, int32_t* d_status, hipStream_t stream) {
-  const AuditLayout A = audit_layout(B, gmax, D, R);
-  const DirectionLayout L = direction_layout(B, gmax, D, R);
-  unsigned char* ws = static_cast<unsigned char*>(workspace);
-  double* gram = reinterpret_cast<double*>(ws + L.gram_off);
-  float* delta = reinterpret_cast<float*>(ws + L.delta_off);
-  float* dsum = reinterpret_cast<float*>(ws + L.dsum_off);
-  double* cpart = reinterpret_cast<double*>(ws + L.cpart_off);
-
-  int st = launch_gram(B, nv, gmax, offsets, D, scores, ld, gram, ws + L.gram_part_off, d_status,
-                       stream);
-  if (st != PAIR_OK) return st;
-  const int64_t grid = B * A.nwg;
-  if (grid > 0x7fffffffLL) return PAIR_ERANGE;
-#define PAIR_DIR(KP_)                                                                           \
-  hipLaunchKernelGGL(audit_coeffs_kernel<KP_>, dim3((unsigned)grid), dim3(kCoefThreads), 0,      \
-                     stream, B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, seed, rep0, 0,  \
-                     R, A.nwg, A.rrows, delta, dsum, nullptr, d_status);                        \
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;                                        \
-  hipLaunchKernelGGL(audit_cosine_kernel<KP_>, dim3((unsigned)grid), dim3(kCosThreads), 0,       \
-                     stream, B, nv, gmax, offsets, rewards, R, A.nwg, A.rrows, delta, gram,       \
-                     cpart, target_norm)
-  switch (A.ks) {
-    case 1: PAIR_DIR(16); break;
-    case 2: PAIR_DIR(32); break;
-    case 3: PAIR_DIR(48); break;
-    default: PAIR_DIR(64); break;
-  }
-#undef PAIR_DIR
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-  hipLaunchKernelGGL(audit_cosine_final_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0,
-                     stream, B, nv, gmax, offsets, R, A.nwg, cpart, cosine);
-  return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
+  return launch_any<true>(AuditArgs{B, nv, gmax, offsets, D, scores, ld, rewards, p, pi_w, rule,
+                                    wmax, seed, rep0, 0, R, cosine, target_norm, nullptr, nullptr,
+                                    workspace, d_status, stream});
 }
 
 int launch_audit(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, int64_t D,
@@ -938,61 +891,9 @@ int launch_audit(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, in
                  const float* pi_w, int32_t rule, float wmax, uint64_t seed, int64_t rep0,
                  int64_t pbase, int64_t R, double* mse, double* bias_norm, float* rep_sqerr,
                  int32_t* edge_count, void* workspace, int32_t* d_status, hipStream_t stream) {
-  const AuditLayout L = audit_layout(B, gmax, D, R);
-  unsigned char* ws = static_cast<unsigned char*>(workspace);
-  float* delta = reinterpret_cast<float*>(ws + L.delta_off);
-  float* epart = reinterpret_cast<float*>(ws + L.epart_off);
-  float* dsum = reinterpret_cast<float*>(ws + L.dsum_off);
-  double* rpart = reinterpret_cast<double*>(ws + L.rpart_off);
-  float* ebar = reinterpret_cast<float*>(ws + L.ebar_off);
-  int32_t* live = reinterpret_cast<int32_t*>(ws + L.live_off);
-  const uint16_t* s = static_cast<const uint16_t*>(scores);
-
-  // Every grid size is checked before the first launch.
-  const int64_t coef_grid = B * L.nwg;
-  const int64_t grid = round_up(B * L.nslices, 8);
-  const int64_t sq_grid = B * L.nsq;
-  if (coef_grid > 0x7fffffffLL || B + 1 > 0x7fffffffLL || grid > 0x7fffffffLL ||
-      sq_grid > 0x7fffffffLL)
-    return PAIR_ERANGE;
-#define PAIR_AUDIT_COEFFS(KP_)                                                                  \
-  hipLaunchKernelGGL(audit_coeffs_kernel<KP_>, dim3((unsigned)coef_grid), dim3(kCoefThreads), 0, \
-                     stream, B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, seed, rep0,     \
-                     pbase, R, L.nwg, L.rrows, delta, dsum, edge_count, d_status)
-  switch (L.ks) {
-    case 1: PAIR_AUDIT_COEFFS(16); break;
-    case 2: PAIR_AUDIT_COEFFS(32); break;
-    case 3: PAIR_AUDIT_COEFFS(48); break;
-    default: PAIR_AUDIT_COEFFS(64); break;
-  }
-#undef PAIR_AUDIT_COEFFS
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-
-  hipLaunchKernelGGL(audit_prep_kernel, dim3((unsigned)(B + 1)), dim3(kPrepThreads), 0, stream, B,
-                     nv, gmax, L.kp, offsets, rewards, R, L.rbar, L.nwg, L.rrows, dsum, delta,
-                     live);
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-
-#define PAIR_AUDIT_MFMA(KS_)                                                                   \
-  hipLaunchKernelGGL(audit_mfma_kernel<KS_>, dim3((unsigned)grid), dim3(kMfmaThreads), 0, stream, \
-                     B, nv, gmax, offsets, D, s, ld, L.rrows, L.ntiles, L.nslices, delta, live,   \
-                     epart, d_status)
-  switch (L.ks) {
-    case 1: PAIR_AUDIT_MFMA(1); break;
-    case 2: PAIR_AUDIT_MFMA(2); break;
-    case 3: PAIR_AUDIT_MFMA(3); break;
-    default: PAIR_AUDIT_MFMA(4); break;
-  }
-#undef PAIR_AUDIT_MFMA
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-
-  hipLaunchKernelGGL(audit_sqerr_kernel, dim3((unsigned)sq_grid), dim3(kSqThreads), 0, stream, B,
-                     nv, gmax, offsets, R, L.rbar, L.rrows, L.nslices, L.nsq, epart, live, rpart,
-                     ebar, rep_sqerr);
-  if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-  hipLaunchKernelGGL(audit_final_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream,
-                     B, nv, gmax, offsets, R, L.nsq, rpart, ebar, mse, bias_norm);
-  return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
+  return launch_any<false>(AuditArgs{B, nv, gmax, offsets, D, scores, ld, rewards, p, pi_w, rule,
+                                     wmax, seed, rep0, pbase, R, mse, bias_norm, rep_sqerr,
+                                     edge_count, workspace, d_status, stream});
 }
 
 }  // namespace pair

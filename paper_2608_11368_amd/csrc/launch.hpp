@@ -29,7 +29,9 @@ int launch_wgrad(int64_t B, int64_t nv, const int64_t* offsets, int64_t D, const
                  int32_t dtype, int64_t ld, const float* coeff, float* out, int32_t reduce,
                  int32_t* d_status, hipStream_t stream);
 
+// The workspace a caller is asked for, and the part of it that is written.
 size_t audit_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R);
+size_t audit_need_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R);
 
 // Prompt b of the call is prompt pbase + b of the generator's counter (its
 // design draws are those of that prompt index); 0 for a whole batch.
@@ -70,12 +72,6 @@ int launch_audit_exact(int64_t B, int64_t nv, int32_t gmax, const int64_t* offse
                        const float* pi_w, int32_t rule, float wmax, double* mse,
                        double* bias_norm, double* gram, void* workspace, int32_t* d_status,
                        hipStream_t stream);
-
-// Gram matrices K_b = S_b S_b^T in fp64 ([B][gmax][gmax], entries beyond G_b
-// not written); the workspace is exact_workspace_bytes(B, gmax, D).
-int launch_gram(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, int64_t D,
-                const void* scores, int64_t ld, double* gram, void* workspace, int32_t* d_status,
-                hipStream_t stream);
 
 size_t direction_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R);
 

@@ -42,15 +42,15 @@ int scratch_address(void** out) {
 
 }  // namespace
 
-// Largest number of consecutive prompts whose audit workspace fits the
-// scratch array (0 if not even one prompt does).  The workspace grows with
-// the prompt count, so a bisection finds it.
+// Largest number of consecutive prompts for which what the audit writes fits
+// the scratch array (0 if the workspace size of a single prompt exceeds it).
+// It grows with the prompt count, so a bisection finds it.
 int64_t audit_noalloc_chunk(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   if (audit_workspace_bytes(1, gmax, D, R) > PAIR_AUDIT_SCRATCH_BYTES) return 0;
   int64_t lo = 1, hi = B;
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo + 1) / 2;
-    if (audit_workspace_bytes(mid, gmax, D, R) <= PAIR_AUDIT_SCRATCH_BYTES)
+    if (audit_need_bytes(mid, gmax, D, R) <= PAIR_AUDIT_SCRATCH_BYTES)
       lo = mid;
     else
       hi = mid - 1;

@@ -1,0 +1,119 @@
+"""The audit's Gram path where it can go wrong: group sizes at the edges of
+the 16-row blocks, score widths at the edges of chunks and slices, ragged
+batches that mix the shapes, replicate counts that leave workgroups without
+a slice, and rows whose fp32 products would overflow, vanish or nearly cancel.
+
+Bound: K_ij has exact products and fp32 runs of a few dozen sums, and the
+fold's fp32 coefficients carry a few roundings, so |Delta e_r| is a small
+multiple c of 2^-24 times A_r^2 with A_r = sum_i (|u_ri| + |a_i|) |s_i|, the size
+of what cancels in delta_r S.  c = 4 is used; the reference is the fp64
+oracle's explicit edge sum."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_11368_amd as pair
+import workloads as wl
+from tests.gpu_util import DEV, log, scores_to_host
+
+pytestmark = pytest.mark.gpu
+
+C = 4 * 2.0 ** -24
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    pair.lib()
+
+
+def _case(sizes, D, kind, seed):
+    rng = np.random.default_rng(seed)
+    off = np.zeros(len(sizes) + 1, dtype=np.int64)
+    off[1:] = np.cumsum(sizes)
+    nv = int(off[-1])
+    rewards = rng.random(nv).astype(np.float32)
+    p = rng.uniform(0.2, 1.0, nv).astype(np.float32)
+    ld = (D + 7) // 8 * 8
+    x = np.full((nv, ld), np.nan, dtype=np.float32)
+    x[:, :D] = rng.standard_normal((nv, D))
+    if kind == "huge":
+        x[::2, :D] *= np.float32(2.0 ** 58)
+    elif kind == "tiny":
+        x[:, :D] *= np.float32(2.0 ** -60)
+    elif kind == "mixed":
+        x[::3, :D] *= np.float32(2.0 ** -100)
+        x[1::3, :D] *= np.float32(2.0 ** 40)
+    elif kind == "zero_rows":
+        x[::2, :D] = 0.0
+    elif kind == "common":
+        x[:, :D] += 300.0 * rng.standard_normal(D).astype(np.float32)
+    s = torch.from_numpy(x).to(torch.bfloat16)
+    return off, rewards, p, s, int(max(sizes))
+
+
+@pytest.mark.parametrize("sizes,D,R,kind", [
+    ([2, 15, 16], 1, 5, "normal"), ([16, 3], 511, 65, "normal"), ([16], 512, 600, "normal"),
+    ([17, 2, 16], 513, 64, "normal"), ([32, 31], 2047, 40, "normal"), ([33, 16], 2048, 40, "normal"),
+    ([48, 5, 17, 33], 2049, 70, "normal"), ([49, 16, 32, 48], 4225, 33, "normal"),
+    ([64, 2, 63], 6145, 300, "normal"), ([16, 16], 8193, 20, "normal"), ([16, 9], 1100, 40, "huge"),
+    ([64, 20], 300, 40, "huge"), ([16, 40], 900, 40, "tiny"), ([16, 64, 31], 2100, 40, "mixed"),
+    ([16, 33], 700, 40, "zero_rows"), ([16, 50], 3000, 40, "common")])
+def test_audit_against_oracle(sizes, D, R, kind):
+    off, rewards, p, s, gmax = _case(sizes, D, kind, 17 * D + R)
+    log(f"audit gram {kind} sizes={sizes} D={D} R={R}")
+    nv, B = int(off[-1]), len(sizes)
+    dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
+    sd = s.to(DEV)[:, :D]
+    got = pair.audit(dev[0], sd, dev[1], dev[2], 99, 7, R, gmax, nv=nv)
+    torch.cuda.synchronize()
+    assert int(got["status"].item()) == 0
+    host = scores_to_host(s)[:, :D]
+    want = oracle.audit(off, host, rewards, p, 99, 7, R, gmax=gmax)
+    assert np.array_equal(got["edge_count"].cpu().numpy(), want["edge_count"])
+    d = oracle.design_inclusion(off, p, 99, 7, R, gmax)
+    full, _ = oracle.pair_coeffs(off, rewards)
+    norms = np.sqrt((s[:, :D].double().numpy() ** 2).sum(1))
+    A = np.zeros((B, R))
+    for r in range(R):
+        u, _ = oracle.pair_coeffs(off, rewards, d["mask"][r], d["pi"])
+        A[:, r] = np.add.reduceat((np.abs(u) + np.abs(full)) * norms, off[:-1])
+    e = got["rep_sqerr"].cpu().numpy().astype(np.float64)
+    worst = np.max(np.abs(e - want["rep_sqerr"]) / (C * A ** 2 + 2.0 ** -24 * want["rep_sqerr"]))
+    mse = got["mse"].cpu().numpy()
+    m = np.max(np.abs(mse - want["mse"]) / (C * (A ** 2).mean(1)))
+    # the bias is a norm: |Delta b| b <= Delta(b^2), of the same size
+    bias = got["bias_norm"].cpu().numpy()
+    bb = np.max(np.abs(bias ** 2 - want["bias_norm"] ** 2) / (C * (A ** 2).mean(1)))
+    log(f"  in units of the bound: e {worst:.3f}, mse {m:.3f}, bias^2 {bb:.3f}")
+    assert worst <= 1.0 and m <= 1.0 and bb <= 1.0
+
+
+@pytest.mark.parametrize("R", [1, 255, 256, 257, 2100])
+def test_replicates_past_the_slices_are_drawn(R):
+    """One slice per prompt and more replicates than its workgroup draws:
+    bitwise the e_r and edge counts of a call per replicate range."""
+    off, rewards, p, s, gmax = _case([16, 40, 7], 96, "normal", R)
+    dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
+    sd, nv = s.to(DEV), int(off[-1])
+    one = pair.audit(dev[0], sd, dev[1], dev[2], 5, 3, R, gmax, nv=nv)
+    cut = (R + 1) // 2
+    parts = [pair.audit(dev[0], sd, dev[1], dev[2], 5, 3 + lo, hi - lo, gmax, nv=nv)
+             for lo, hi in ((0, cut), (cut, R)) if hi > lo]
+    for key in ("rep_sqerr", "edge_count"):
+        assert torch.equal(torch.cat([x[key] for x in parts], dim=1), one[key])
+
+
+def test_nonfinite_score_raises_in_any_slice():
+    off, rewards, p, s, gmax = _case([16, 33], 5000, "normal", 4)
+    dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
+    for row, col, v in ((3, 4999, float("inf")), (20, 0, float("nan")), (48, 2500, float("-inf"))):
+        bad = s.clone()
+        bad[row, col] = v
+        got = pair.audit(dev[0], bad.to(DEV), dev[1], dev[2], 5, 0, 20, gmax, nv=int(off[-1]))
+        assert int(got["status"].item()) == pair.ST_NONFINITE
+        other = 1 if row < 16 else 0
+        ok = pair.audit(dev[0], s.to(DEV), dev[1], dev[2], 5, 0, 20, gmax, nv=int(off[-1]))
+        assert torch.equal(got["rep_sqerr"][other], ok["rep_sqerr"][other])
