@@ -267,19 +267,22 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
     const int32_t* gx = gex + b * nsl * (KP + 1);
     double k = 0.0;
     const bool inside = 16 * c < g;   // uniform; entries past g inside a block are 0
+    // Loads past the last slice repeat it (a guarded load would wait for its
+    // turn) and are not added.
     for (int64_t s0 = 0; inside && s0 < nsl; s0 += 16) {
       float v[16];
       int32_t scaled[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const bool in = s0 + q < nsl;
-        v[q] = in ? src[(s0 + q) * (kTiles * 256)] : 0.0f;
-        scaled[q] = (in && skip_equal) ? gx[(s0 + q) * (KP + 1) + KP] : 0;
+        const int64_t sl = s0 + q < nsl ? s0 + q : nsl - 1;
+        v[q] = src[sl * (kTiles * 256)];
+        scaled[q] = gx[sl * (KP + 1) + KP];
       }
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
+        if (s0 + q >= nsl) break;
         double x = (double)v[q];
-        if (scaled[q] != 0) {
+        if (skip_equal && scaled[q] != 0) {   // else the exponents were not written
           const int32_t* row = gx + (s0 + q) * (KP + 1);
           // rows past the prompt's own blocks have no exponent
           x = i < g && j < g ? ldexp(x, row[i] + row[j]) : 0.0;
@@ -370,21 +373,6 @@ __device__ __forceinline__ double group_sum_d(double v) {
   hi = __builtin_amdgcn_permlane32_swap((uint32_t)(w >> 32), (uint32_t)(w >> 32), false, false);
   return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
          __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
-}
-
-// Sums over the 16 lanes of each lane group, the same in all of them.
-__device__ __forceinline__ float row_sum(float v) {
-  v += dpp_f<0xB1>(v);
-  v += dpp_f<0x4E>(v);
-  v += dpp_f<0x141>(v);
-  return v + dpp_f<0x140>(v);
-}
-
-__device__ __forceinline__ double row_sum_d(double v) {
-  v += dpp_d<0xB1>(v);
-  v += dpp_d<0x4E>(v);
-  v += dpp_d<0x141>(v);
-  return v + dpp_d<0x140>(v);
 }
 
 // All ones if bit v of a lane's four indicators is set, else 0.

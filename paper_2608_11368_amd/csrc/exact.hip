@@ -35,6 +35,8 @@ namespace {
 
 constexpr int kFinalThreads = 1024;
 
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct ExactLayout {
@@ -110,9 +112,11 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
     double* __restrict__ gram, int32_t* d_status) {
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
-  __shared__ __align__(16) double K[KP * KP];
-  __shared__ double Ac[KP * KP];   // A_ij: coefficient of s_i in v_ij; C_ij = A_ji
-  __shared__ __align__(16) double X[KP * KP];
+  constexpr int kRow = KP + 1;   // row stride in LDS: column walks spread over the banks
+  constexpr int kOwn = (kTiles + kFinalThreads / 256 - 1) / (kFinalThreads / 256);
+  __shared__ double K[KP * kRow];
+  __shared__ double Ac[KP * kRow];   // A_ij: coefficient of s_i in v_ij; C_ij = A_ji
+  __shared__ double X[KP * kRow];
   __shared__ double beta[KP], pd[KP], rd[KP];
   __shared__ double sh[kFinalThreads / kWave];
   const int64_t b = blockIdx.x;
@@ -127,10 +131,37 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
     if (tid < gi && !p_in_range(p[o0 + tid])) raise_status(d_status, PAIR_ST_P_RANGE);
   }
   bool nonfinite = false;
-  // Slice partials added in slice order, eight loads in flight; thread e of a
-  // group of 256 holds entry e of the group's tiles.
+  // Slice partials added in slice order; thread e of a group of 256 holds
+  // entry e of the group's tiles, eight slices of all of them in flight (one
+  // tile after the other took 12 us longer at 64 rows and 32 slices).
   const int e = tid & 255;
-  for (int t = tid / 256; t < kTiles; t += kFinalThreads / 256) {
+  double sum[kOwn];
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) sum[u] = 0.0;
+  const float* src = part + b * nsl * (kTiles * 256) + e;
+  // Loads past the last slice or tile repeat it (a guarded load would wait for
+  // its turn) and are not added.
+  for (int64_t s0 = 0; s0 < nsl; s0 += 8) {
+    float v[kOwn][8];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      int t = tid / 256 + u * (kFinalThreads / 256);
+      t = t < kTiles ? t : kTiles - 1;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int64_t sl = s0 + q < nsl ? s0 + q : nsl - 1;
+        v[u][q] = src[(sl * kTiles + t) * 256];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sum[u] += s0 + q < nsl ? (double)v[u][q] : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int t = tid / 256 + u * (kFinalThreads / 256);
+    if (t >= kTiles) continue;
     int ta = 0, tc = 0;
 #pragma unroll
     for (int x = 0; x < KS; ++x)
@@ -142,25 +173,16 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
         }
     const int i = 16 * ta + 4 * (e >> 6) + (e & 3), j = 16 * tc + ((e >> 2) & 15);
     double k = 0.0;
-    if (i < gi && j < gi) {
-      const float* src = part + (b * nsl * kTiles + t) * 256 + e;
-      int64_t s = 0;
-      for (; s + 8 <= nsl; s += 8) {
-        float v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = src[(s + q) * (kTiles * 256)];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) k += (double)v[q];
-      }
-      for (; s < nsl; ++s) k += (double)src[s * (kTiles * 256)];
+    if (i < gi && j < gi) {   // tiles past the group's blocks were not written
+      k = sum[u];
       if (!isfinite(k)) nonfinite = true;
       if (gram != nullptr) {
         gram[(b * gmax + i) * (int64_t)gmax + j] = k;
         if (ta != tc) gram[(b * gmax + j) * (int64_t)gmax + i] = k;
       }
     }
-    K[i * KP + j] = k;
-    if (ta != tc) K[j * KP + i] = k;
+    K[i * kRow + j] = k;
+    if (ta != tc) K[j * kRow + i] = k;
   }
   if (nonfinite) raise_status(d_status, PAIR_ST_NONFINITE);
   __syncthreads();
@@ -192,65 +214,67 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
       }
       a = 0.5 * (rd[i] - rd[j]) * wi;
     }
-    Ac[idx] = a;
+    Ac[i * kRow + j] = a;
   }
   if (bad) raise_status(d_status, PAIR_ST_RHO_RANGE);
   __syncthreads();
 
-  const double M = 0.5 * (double)gi * (double)(gi - 1);
-  if (tid < KP) {
-    double be = 0.0;
-    if (tid < gi)
-      for (int j = 0; j < gi; ++j)
-        if (j != tid) be += pd[tid] * pd[j] * Ac[tid * KP + j] - 0.5 * (rd[tid] - rd[j]);
-    beta[tid] = be / M;
-  }
-  __syncthreads();
-
   // X_ij = p_j C_ij off the diagonal and X_ii = sum_j p_j A_ij, the
-  // coefficients of sum_j p_j v_ij.
+  // coefficients of sum_j p_j v_ij; the row sums by 16 lanes per row.
+  const double M = 0.5 * (double)gi * (double)(gi - 1);
   for (int idx = tid; idx < KP * KP; idx += kFinalThreads) {
     const int i = idx / KP, j = idx - i * KP;
-    if (i != j) X[idx] = pd[j] * Ac[j * KP + i];   // zero past the group
+    if (i != j) X[i * kRow + j] = pd[j] * Ac[j * kRow + i];   // zero past the group
   }
-  if (tid < KP) {
-    double d = 0.0;
-    for (int j = 0; j < gi; ++j) d += pd[j] * Ac[tid * KP + j];
-    X[tid * KP + tid] = d;
+  {
+    const int i = tid / 16;
+    double be = 0.0, d = 0.0;
+    if (i < gi)
+      for (int j = tid & 15; j < gi; j += 16) {
+        const double a = Ac[i * kRow + j];   // zero for j = i
+        be += pd[i] * pd[j] * a - 0.5 * (rd[i] - rd[j]);
+        d += pd[j] * a;
+      }
+    be = row_sum_d(be);
+    d = row_sum_d(d);
+    if (i < KP && (tid & 15) == 0) {
+      beta[i] = be / M;
+      X[i * kRow + i] = d;
+    }
   }
   __syncthreads();
 
-  // beta^T K beta, the pair terms and the shared-vertex terms; the products
-  // (X K)_ij in blocks of 2 x 2 per thread.
+  // beta^T K beta and the pair terms.
   double bk = 0.0, tr = 0.0;
   for (int idx = tid; idx < gi * gi; idx += kFinalThreads) {
     const int i = idx / gi, j = idx - i * gi;
-    bk += beta[i] * beta[j] * K[i * KP + j];
+    bk += beta[i] * beta[j] * K[i * kRow + j];
     if (j <= i) continue;
-    const double aij = Ac[i * KP + j], cij = Ac[j * KP + i];
+    const double aij = Ac[i * kRow + j], cij = Ac[j * kRow + i];
     const double rho = pd[i] * pd[j];
-    const double nn = aij * aij * K[i * KP + i] + 2.0 * aij * cij * K[i * KP + j] +
-                      cij * cij * K[j * KP + j];
+    const double nn = aij * aij * K[i * kRow + i] + 2.0 * aij * cij * K[i * kRow + j] +
+                      cij * cij * K[j * kRow + j];
     // the pair's own term, less its share of both vertices' squares
     tr += (rho * (1.0 - rho) - pd[i] * (1.0 - pd[i]) * pd[j] * pd[j] -
            pd[j] * (1.0 - pd[j]) * pd[i] * pd[i]) * nn;
   }
-  const int hb = (gi + 1) / 2;
-  for (int idx = tid; idx < hb * hb; idx += kFinalThreads) {
-    const int i = 2 * (idx / hb), j = 2 * (idx % hb);
-    double y[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-    for (int k = 0; k < gi; ++k) {
-      const double2 kk = *reinterpret_cast<const double2*>(&K[k * KP + j]);
-      const double x0 = X[i * KP + k], x1 = X[(i + 1) * KP + k];
-      y[0][0] = __builtin_fma(x0, kk.x, y[0][0]);
-      y[0][1] = __builtin_fma(x0, kk.y, y[0][1]);
-      y[1][0] = __builtin_fma(x1, kk.x, y[1][0]);
-      y[1][1] = __builtin_fma(x1, kk.y, y[1][1]);
-    }
+  // The shared-vertex terms: Y = X K tile by tile on the fp64 matrix cores, a wave per 16 x 16 tile;
+  // lane l holds rows 4 v + l / 16 and column l % 16 of it.  Rows and columns
+  // past the group are zero.
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
+  const int col = lane & 15, grp = lane >> 4;
+  for (int t = wave; t < KS * KS; t += kFinalThreads / kWave) {
+    const int r0 = 16 * (t / KS), c0 = 16 * (t % KS);
+    f64x4_t y = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int u = 0; u < 2; ++u)   // rows and columns past the group hold zeros
-      tr += pd[i + u] * (1.0 - pd[i + u]) *
-            (y[u][0] * X[(i + u) * KP + j] + y[u][1] * X[(i + u) * KP + j + 1]);
+    for (int s = 0; s < KP / 4; ++s)
+      y = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(r0 + col) * kRow + 4 * s + grp],
+                                               K[(4 * s + grp) * kRow + c0 + col], y, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = r0 + 4 * v + grp;
+      tr += pd[i] * (1.0 - pd[i]) * y[v] * X[i * kRow + c0 + col];
+    }
   }
   const double bb = block_sum(bk, sh);
   const double tt = block_sum(tr, sh);
