@@ -26,14 +26,13 @@
 //                   100-500).  The joint block uses the difference formula
 //                   when the two odds differ by more than 1e-5 relative and
 //                   the direct leave-two-out polynomial otherwise.
-//  cps_draw_kernel  lane = replicate.  The workgroup builds the suffix table
-//                   E[i][k] = e_k(w_i .. w_{G-1}) in LDS (lane k, units from
-//                   the last); each lane then walks the units in order and
+//  cps_draw_kernel  lane = replicate.  With E[i][k] = e_k(w_i .. w_{G-1}) (built from
+//                   the last unit), each lane walks the units in order and
 //                   selects unit i with probability
 //                   w_i E[i+1][k-1] / E[i][k], k the units still to select,
 //                   comparing the top 32 bits of Philox4x64-10 word (i & 3) at
 //                   counter (replicate, prompt, i >> 2, 0) with that
-//                   probability times 2^32.  The table and the thresholds use
+//                   probability times 2^32.  The polynomials and the thresholds use
 //                   unfused fp64 operations in a fixed order, so each draw is
 //                   a deterministic function of (seed, replicate, prompt, w).
 #include "common.hpp"
@@ -285,73 +284,96 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
   }
 }
 
+// The draw of up to kDrawReps replicates of one prompt.  The selection
+// probability depends on (unit, units still to select) alone, so wave 0 builds
+// its thresholds once for the workgroup's replicates: lane k carries E[i][k] in a register (one
+// whole-wave DPP shift per unit), and the division is beside that chain.  A
+// replicate then costs one LDS read and one comparison per unit.  The taken units gather in
+// a 64-bit mask per lane, and the wave stores its replicates' rows four bytes at a time,
+// 16 lanes or fewer to a row, where a byte per lane and unit would touch a
+// line per replicate each time.
+// B = 512, G in 2..64, R = 256: 58 us with a division per unit and
+// replicate, the table built per 64 replicates and byte stores; 29 us so.
+constexpr int kDrawReps = 256;
+
 template <int KP>
-__global__ __launch_bounds__(kWave) void cps_draw_kernel(
+__global__ __launch_bounds__(kDrawReps) void cps_draw_kernel(
     int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
     const double* __restrict__ w, const int32_t* __restrict__ n_in, uint64_t seed, int64_t rep0,
     int64_t R, int64_t nwg, uint8_t* __restrict__ mask, int32_t* __restrict__ edge_count,
     int32_t* d_status) {
-  __shared__ double E[(KP + 1) * (KP + 1)];   // E[i][k], row stride KP + 1
-  __shared__ double wl[KP];
+  constexpr int S = KP + 1;
+  __shared__ double thr[KP * S];   // [i][k]: 2^32 x the probability of taking unit i, k left
   const int64_t b = blockIdx.x / nwg;
   const int64_t chunk = blockIdx.x - b * nwg;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
   int64_t o0, g64;
-  if (!prompt_bounds(offsets, b, nv, 1, gmax, &o0, &g64, d_status, chunk == 0 && lane == 0))
+  if (!prompt_bounds(offsets, b, nv, 1, gmax, &o0, &g64, d_status, chunk == 0 && tid == 0))
     return;
   const int g = (int)g64;
   const int n = n_in[b];
-  bool bad = n < 0 || n > g;
-  if (!bad && lane < g) {
-    const double wv = w[o0 + lane];
-    bad = !(wv > 0.0 && wv < 1e300);
-    wl[lane] = wv;
-  }
-  if (__ballot(bad) != 0ull) {
-    if (chunk == 0 && lane == 0) raise_status(d_status, PAIR_ST_P_RANGE);
+  // Every wave reads the odds: the decision to leave is the whole workgroup's.
+  const double wv = lane < g ? w[o0 + lane] : 1.0;
+  if (n < 0 || n > g || __ballot(!(wv > 0.0 && wv < 1e300)) != 0ull) {
+    if (chunk == 0 && tid == 0) raise_status(d_status, PAIR_ST_P_RANGE);
     return;
   }
-  constexpr int S = KP + 1;
   const bool all_or_none = n == 0 || n == g;   // no randomness: the table is not needed
   if (!all_or_none) {
-    if (lane <= n) E[g * S + lane] = lane == 0 ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  for (int i = all_or_none ? -1 : g - 1; i >= 0; --i) {
-    if (lane <= n) {
-      double v = 1.0;
-      if (lane >= 1) {
-        const double tmul = __dmul_rn(wl[i], E[(i + 1) * S + lane - 1]);
-        v = __dadd_rn(E[(i + 1) * S + lane], tmul);
+    if (tid < kWave) {
+      double col = lane == 0 ? 1.0 : 0.0;   // E[i + 1][lane]
+      for (int i = g - 1; i >= 0; --i) {
+        const double num = __dmul_rn(readlane_d(wv, i), dpp_d<0x138>(col));   // wave_shr:1
+        col = __dadd_rn(col, num);
+        if (lane >= 1 && lane <= n)
+          thr[i * S + lane] = __dmul_rn(__ddiv_rn(num, col), 4294967296.0);
+        if (lane == 0) thr[i * S] = 0.0;   // none left: never taken
       }
-      E[i * S + lane] = v;
     }
     __syncthreads();
   }
 
-  const int64_t r = chunk * kWave + lane;
-  if (r >= R) return;
-  const uint64_t rg = (uint64_t)(rep0 + r);
-  uint8_t* mrow = mask + r * nv + o0;
-  int k = n;
-  Philox4x64 x;
-  for (int i = 0; i < g; ++i) {
-    if (all_or_none) {
-      mrow[i] = (uint8_t)(n == g ? 1 : 0);
-      continue;
+  const int64_t r0 = chunk * blockDim.x + (tid - lane);   // the wave's first replicate
+  if (r0 >= R) return;
+  const int nr = (int)(R - r0 < kWave ? R - r0 : kWave);
+  uint64_t bits = n == g ? ~0ull : 0ull;
+  if (!all_or_none) {
+    const PhiloxRep pr = philox_rep((uint64_t)(rep0 + r0 + lane));
+    int k = n;
+    for (int i = 0; i < g; i += 4) {
+      const Philox4x64 x = philox_quad(pr, (uint64_t)b, (uint64_t)(i >> 2), seed);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (i + e < g) {
+          const bool take = (double)(x.w[e] >> 32) < thr[(i + e) * S + k];
+          bits |= (uint64_t)take << (i + e);
+          k -= take ? 1 : 0;
+        }
+      }
     }
-    if ((i & 3) == 0) x = philox4x64_10(rg, (uint64_t)b, (uint64_t)(i >> 2), 0ull, seed, 0ull);
-    const double u = (double)(philox_word(x, i & 3) >> 32);
-    int take = 0;
-    if (k > 0) {
-      const double num = __dmul_rn(wl[i], E[(i + 1) * S + k - 1]);
-      const double prob = __ddiv_rn(num, E[i * S + k]);
-      take = u < __dmul_rn(prob, 4294967296.0) ? 1 : 0;
-    }
-    mrow[i] = (uint8_t)take;
-    k -= take;
   }
-  if (edge_count != nullptr) edge_count[r * B + b] = n * (n - 1) / 2;
+  if (edge_count != nullptr && lane < nr) edge_count[(r0 + lane) * B + b] = n * (n - 1) / 2;
+  // Row r of the mask: nq lanes of four units each, 64 / nq rows at a time.
+  const int nq = (g + 3) >> 2;
+  const int per = kWave / nq;
+  const int row = lane / nq, q = lane - row * nq;
+  const int units = g - 4 * q < 4 ? g - 4 * q : 4;
+  uint8_t* m = mask + r0 * nv + o0 + 4 * q;
+  for (int base = 0; base < nr; base += per) {
+    const int r = base + row;
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)bits, r & (kWave - 1), kWave);
+    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(bits >> 32), r & (kWave - 1), kWave);
+    if (row >= per || r >= nr) continue;
+    const uint32_t v = ((q < 8 ? lo : hi) >> (4 * (q & 7))) & 0xfu;
+    const uint32_t bytes = (v & 1u) | (v & 2u) << 7 | (v & 4u) << 14 | (v & 8u) << 21;
+    uint8_t* dst = m + (int64_t)r * nv;
+    if (units == 4) {
+      __builtin_memcpy(dst, &bytes, 4);
+    } else {
+      for (int e = 0; e < units; ++e) dst[e] = (uint8_t)(bytes >> (8 * e));
+    }
+  }
 }
 
 }  // namespace
@@ -377,11 +399,13 @@ int launch_cps_draw(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets,
                     const int32_t* n, uint64_t seed, int64_t rep0, int64_t R, uint8_t* mask,
                     int32_t* edge_count, int32_t* d_status, hipStream_t stream) {
   const int ks = (gmax + 15) / 16;
-  const int64_t nwg = (R + kWave - 1) / kWave;
+  // Replicates per workgroup: whole waves, no more of them than R needs.
+  const int64_t reps = R < kDrawReps ? (R + kWave - 1) / kWave * kWave : kDrawReps;
+  const int64_t nwg = (R + reps - 1) / reps;
   const int64_t grid = B * nwg;
   if (grid > 0x7fffffffLL) return PAIR_ERANGE;
 #define PAIR_CPS_DRAW(KP_)                                                                     \
-  hipLaunchKernelGGL(cps_draw_kernel<KP_>, dim3((unsigned)grid), dim3(kWave), 0, stream, B, nv, \
+  hipLaunchKernelGGL(cps_draw_kernel<KP_>, dim3((unsigned)grid), dim3((unsigned)reps), 0, stream, B, nv, \
                      gmax, offsets, w, n, seed, rep0, R, nwg, mask, edge_count, d_status)
   switch (ks) {
     case 1: PAIR_CPS_DRAW(16); break;
