@@ -82,15 +82,32 @@ __device__ __forceinline__ PhiloxRep philox_rep(uint64_t r) {
   return q;
 }
 
-__device__ __forceinline__ Philox4x64 philox_quad(const PhiloxRep& q, uint64_t prompt,
-                                                  uint64_t quad, uint64_t seed) {
+// The quad's part of the first two rounds: with a replicate's, the state
+// after them is (hi1 ^ c0, lo1, c2 ^ lo0, c3).
+struct PhiloxQuad {
+  uint64_t c0, c2, c3;
+};
+
+__device__ __forceinline__ PhiloxQuad philox_quad_part(uint64_t prompt, uint64_t quad,
+                                                       uint64_t seed) {
   const uint64_t m0 = 0xD2E7470EE14C6C93ull, m1 = 0xCA5A826395121157ull;
   const uint64_t w0 = 0x9E3779B97F4A7C15ull, w1 = 0xBB67AE8584CAA73Bull;
   uint64_t uh, ul, vh, vl;
   mulhilo64(m1, quad, &uh, &ul);                   // round 1: (uh ^ prompt ^ seed, ul, hi0, lo0)
   mulhilo64(m0, uh ^ prompt ^ seed, &vh, &vl);     // round 2
+  PhiloxQuad o;
+  o.c0 = ul ^ (seed + w0);
+  o.c2 = vh ^ w1;
+  o.c3 = vl;
+  return o;
+}
+
+// Rounds 3 to 10 on the state after round 2.
+__device__ __forceinline__ Philox4x64 philox_rounds_3_10(uint64_t c0, uint64_t c1, uint64_t c2,
+                                                         uint64_t c3, uint64_t seed) {
+  const uint64_t m0 = 0xD2E7470EE14C6C93ull, m1 = 0xCA5A826395121157ull;
+  const uint64_t w0 = 0x9E3779B97F4A7C15ull, w1 = 0xBB67AE8584CAA73Bull;
   uint64_t k0 = seed + w0, k1 = w1;
-  uint64_t c0 = q.hi1 ^ ul ^ k0, c1 = q.lo1, c2 = vh ^ q.lo0 ^ k1, c3 = vl;
 #pragma unroll
   for (int round = 2; round < 10; ++round) {
     k0 += w0;
@@ -111,6 +128,12 @@ __device__ __forceinline__ Philox4x64 philox_quad(const PhiloxRep& q, uint64_t p
   o.w[2] = c2;
   o.w[3] = c3;
   return o;
+}
+
+__device__ __forceinline__ Philox4x64 philox_quad(const PhiloxRep& q, uint64_t prompt,
+                                                  uint64_t quad, uint64_t seed) {
+  const PhiloxQuad h = philox_quad_part(prompt, quad, seed);
+  return philox_rounds_3_10(q.hi1 ^ h.c0, q.lo1, h.c2 ^ q.lo0, h.c3, seed);
 }
 
 // Output word q of a block, selected without a dynamic index: indexing the
