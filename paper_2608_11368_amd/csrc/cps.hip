@@ -19,7 +19,7 @@
 //                   sum_k prefix_i[k] suffix_i[n-1-k] (all terms positive);
 //                   the log-odds then take a Newton step whose Hessian is
 //                   the design covariance pi_ij - pi_i pi_j (solved by
-//                   Gaussian elimination in LDS, lane = row), halved until
+//                   Gauss-Jordan elimination in registers, lane = row), halved until
 //                   the concave objective rises, until every pi_i is within
 //                   1e-12 of its target (3-8 evaluations where a plain
 //                   fixed point w_i <- w_i pi_target_i / pi_i takes
@@ -80,21 +80,80 @@ constexpr int kS = 65;
 template <int KP>
 __device__ __forceinline__ void esp_tables(double w, int g, int n, int lane, double* Pf,
                                            double* Sf) {
-  double col = lane == 0 ? 1.0 : 0.0;
-  if (lane <= n) Pf[lane] = col;
-  for (int m = 0; m < g; ++m) {
-    const double wm = readlane_d(w, m);
-    col = __dadd_rn(col, __dmul_rn(wm, dpp_d<0x138>(col)));   // wave_shr:1
-    if (lane <= n) Pf[(m + 1) * kS + lane] = col;
+  // The two serial chains run side by side.
+  double pre = lane == 0 ? 1.0 : 0.0, suf = pre;
+  if (lane <= n) {
+    Pf[lane] = pre;
+    Sf[(g - 1) * kS + lane] = suf;
   }
-  col = lane == 0 ? 1.0 : 0.0;
-  if (lane <= n) Sf[(g - 1) * kS + lane] = col;
-  for (int m = g - 1; m >= 1; --m) {
-    const double wm = readlane_d(w, m);
-    col = __dadd_rn(col, __dmul_rn(wm, dpp_d<0x138>(col)));
-    if (lane <= n) Sf[(m - 1) * kS + lane] = col;
+  for (int m = 0; m < g; ++m) {
+    const int u = g - 1 - m;
+    const double wp = readlane_d(w, m), ws = readlane_d(w, u);
+    pre = __dadd_rn(pre, __dmul_rn(wp, dpp_d<0x138>(pre)));   // wave_shr:1
+    suf = __dadd_rn(suf, __dmul_rn(ws, dpp_d<0x138>(suf)));
+    if (lane <= n) {
+      Pf[(m + 1) * kS + lane] = pre;
+      if (u >= 1) Sf[(u - 1) * kS + lane] = suf;
+    }
   }
   __syncthreads();
+}
+
+// 1 / x to rounding for normal x: the hardware's estimate and a step of third order.
+__device__ __forceinline__ double recip_d(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// Step K and all after it of the elimination of the Newton system, without
+// pivoting (the matrix is symmetric positive definite).  Lane i owns row i.  Every other
+// row is cleared of the pivot column, rows above included (Gauss-Jordan: the
+// lanes run anyway, and no back substitution is left).  The rows and columns from the pivot on
+// stay symmetric, so the pivot row is the pivot column: one store of a[K] by
+// all lanes, read back as broadcasts, kChunk entries in flight while the last
+// ones are used.  The steps are unrolled, so that register indices are constants
+// and no row moves.  One wave, whose LDS accesses keep their order: no waits
+// but for the data.
+constexpr int kChunk = 16;
+
+template <int KP, int K>
+__device__ __forceinline__ void eliminate(int g, int lane, double (&a)[KP], double& x,
+                                          double& inv_piv, double* buf) {
+  if (K >= g) return;
+  double* v = buf + (K & 1) * kWave;
+  v[lane] = a[K];
+  __builtin_amdgcn_wave_barrier();
+  constexpr int C0 = (K + 1) & ~1;   // pairs of entries, 16 bytes a load
+  constexpr int N = (KP - C0 + kChunk - 1) / kChunk;
+  double u[2][kChunk];
+#pragma unroll
+  for (int e = 0; e < kChunk; ++e)
+    if (C0 + e < KP) u[0][e] = v[C0 + e];
+  __builtin_amdgcn_sched_barrier(0);
+  const double inv = recip_d(readlane_d(a[K], K));
+  const double xk = readlane_d(x, K);
+  const double m = lane == K ? 0.0 : a[K] * inv;
+  inv_piv = lane == K ? inv : inv_piv;
+  x = fma(-m, xk, x);
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e)
+      if (C0 + (c + 1) * kChunk + e < KP) u[(c + 1) & 1][e] = v[C0 + (c + 1) * kChunk + e];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < kChunk; ++e) {
+      const int j = C0 + c * kChunk + e;
+      if (j > K && j < KP) {
+        a[j] = fma(-m, u[c & 1][e], a[j]);
+        // used here: left to itself the compiler moves the sum behind the
+        // next step's exit and keeps its operands, which spills
+        asm volatile("" : "+v"(a[j]));
+      }
+    }
+  }
+  if constexpr (K + 1 < KP) eliminate<KP, K + 1>(g, lane, a, x, inv_piv, buf);
 }
 
 template <int KP>
@@ -103,7 +162,7 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
     const float* __restrict__ pi_target, double* __restrict__ w_out, int32_t* __restrict__ n_out,
     float* __restrict__ pi_joint, int32_t* __restrict__ iters, int32_t* d_status) {
   __shared__ double Pf[(KP + 1) * kS];
-  __shared__ double Sf[KP * kS];
+  __shared__ __attribute__((aligned(16))) double Sf[KP * kS];
   const int64_t b = blockIdx.x;
   const int lane = threadIdx.x;
   int64_t o0, g64;
@@ -182,68 +241,50 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
     err0 = err;
     have_base = true;
 
-    // Row `lane` of H + 1 1^T / g, in registers (entry j in a[j], zero
-    // beyond the group).  Off the diagonal pi_ij comes from the difference
+    // Column `lane` of H + 1 1^T / g (it is symmetric), first in LDS: in
+    // registers the loop over j would be unrolled KP times, twice, past the
+    // instruction cache.  Off the diagonal pi_ij comes from the difference
     // formula; where two odds agree to 1e-6 it is numerically unreliable, and
     // those entries share what the row identity
     // sum_{j != i} pi_ij = (n - 1) pi_i leaves (exact for equal odds).
     const double inv_g = 1.0 / (double)g;
-    double a[KP];
     double known = 0.0;
     int nclose = 0;
+    for (int j0 = 0; j0 < g; j0 += 4) {
 #pragma unroll
-    for (int j = 0; j < KP; ++j) {
-      const double wj = readlane_d(w, j), pj = readlane_d(pi, j);
-      const bool off = unit && j < g && j != lane;
-      const bool sep = fabs(wj - w) > 1e-6 * fmax(wj, w);
-      const double pij = (off && sep) ? (wj * pi - w * pj) / (wj - w) : 0.0;
-      known += pij;
-      nclose += (off && !sep) ? 1 : 0;
-      a[j] = (off && sep) ? pij - pi * pj + inv_g
-                          : ((unit && j == lane) ? pi * (1.0 - pi) + inv_g : 0.0);
+      for (int s = 0; s < 4; ++s) {
+        const int j = j0 + s;
+        const double wj = readlane_d(w, j), pj = readlane_d(pi, j);
+        const bool off = unit && j < g && j != lane;
+        const bool sep = fabs(wj - w) > 1e-6 * fmax(wj, w);
+        // Formed in every lane and then selected: a branch per entry would
+        // keep the entries from overlapping.
+        double pij = (wj * pi - w * pj) * recip_d(wj - w);
+        asm("" : "+v"(pij));
+        pij = (off && sep) ? pij : 0.0;
+        known += pij;
+        nclose += (off && !sep) ? 1 : 0;
+        double h = pij - pi * pj + inv_g, hd = pi * (1.0 - pi) + inv_g;
+        asm("" : "+v"(h), "+v"(hd));
+        h = (off && sep) ? h : 0.0;
+        Pf[j * kS + lane] = (unit && j == lane) ? hd : h;
+      }
     }
     if (__ballot(nclose > 0) != 0ull) {
       const double share = nclose > 0 ? ((double)(n - 1) * pi - known) / (double)nclose : 0.0;
-#pragma unroll
-      for (int j = 0; j < KP; ++j) {
+      for (int j = 0; j < g; ++j) {
         const double wj = readlane_d(w, j), pj = readlane_d(pi, j);
-        const bool close = unit && j < g && j != lane && !(fabs(wj - w) > 1e-6 * fmax(wj, w));
-        if (close) a[j] = share - pi * pj + inv_g;
+        const bool close = unit && j != lane && !(fabs(wj - w) > 1e-6 * fmax(wj, w));
+        if (close) Pf[j * kS + lane] = share - pi * pj + inv_g;
       }
     }
-    // Gaussian elimination without pivoting (the matrix is symmetric
-    // positive definite).  Lane i owns row i and right-hand side entry x_i.
-    // At step k every row is shifted left by k, so the pivot column is
-    // always a[0] and all register indices are compile-time constants; the
-    // pivot row (row k, shifted) and its right-hand side are kept in LDS
-    // (U, xs) for the back substitution.  Rows at or above the pivot compute
-    // values that are never used.
-    double x = unit ? t - pi : 0.0;
-    double* U = Pf;          // U[k][j] = row k's entry k + j after step k
-    double* xs = Sf;         // right-hand side of pivot row k
-    for (int k = 0; k < g; ++k) {
-      if (lane == k) {
+    for (int j = (g + 3) & ~3; j < KP; ++j) Pf[j * kS + lane] = 0.0;
+    double a[KP];   // a lane reads what it wrote
 #pragma unroll
-        for (int j = 0; j < KP; ++j) U[k * KP + j] = a[j];
-        xs[k] = x;
-      }
-      __syncthreads();
-      const double xk = readlane_d(x, k);
-      const double m = a[0] / U[k * KP];
-#pragma unroll
-      for (int j = 1; j < KP; ++j) a[j - 1] = a[j] - m * U[k * KP + j];
-      a[KP - 1] = 0.0;
-      x -= m * xk;
-    }
-    // Back substitution, one column of U per step: lane i keeps the still
-    // unresolved part y_i of its equation and ends holding x_i.
-    double y = unit ? xs[lane] : 0.0;
-    for (int k = g - 1; k >= 0; --k) {
-      const double xk = readlane_d(y, k) / U[k * KP];
-      if (lane == k) y = xk;
-      if (lane < k) y -= U[lane * KP + (k - lane)] * xk;
-    }
-    x = y;
+    for (int j = 0; j < KP; ++j) a[j] = Pf[j * kS + lane];
+    double x = unit ? t - pi : 0.0, inv_piv = 0.0;
+    eliminate<KP, 0>(g, lane, a, x, inv_piv, Sf);
+    x *= inv_piv;
     d = unit ? x : 0.0;
     slope = wave_sum_d(unit ? (t - pi) * d : 0.0);
     step = 1.0;
@@ -260,26 +301,28 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
   }
 
   if (pi_joint != nullptr) {
-    // Row i of the joint block by lane i, from the last evaluation's pi and
+    // Row j of the joint block at step j: lane i holds pi_ij = pi_ji, so the
+    // wave stores a run (a row per lane would touch a line per lane).  It is
+    // taken from the last evaluation's pi and
     // e_n(w).  The difference formula loses about eps / gap of relative
     // accuracy, so it is used where the two odds differ by more than 1e-5
     // (error below 1e-8, under the fp32 output's rounding); closer pairs
     // take the leave-two-out polynomial.
-    float* row = pi_joint + (b * (int64_t)gmax + lane) * gmax;
+    float* col = pi_joint + b * (int64_t)gmax * gmax + lane;
     for (int j = 0; j < gmax; ++j) {
       const double wj = readlane_d(w, j < g ? j : 0), pj = readlane_d(pi, j < g ? j : 0);
       const bool pair_ij = unit && j < g && j != lane;
       const bool sep = fabs(wj - w) > 1e-5 * fmax(wj, w);
-      double v = 0.0;
-      if (unit && j == lane) v = pi;
-      if (pair_ij && sep) v = (wj * pi - w * pj) / (wj - w);
+      double pij = 0.0;
+      if (unit && j == lane) pij = pi;
+      if (pair_ij && sep) pij = (wj * pi - w * pj) / (wj - w);
       const bool direct = pair_ij && !sep && n >= 2;
       if (__ballot(direct) != 0ull) {
         double e2[KP];
         esp_excl<KP>(w, g, n - 2, lane, j, e2);   // w of lane j is excluded too
-        if (direct) v = w * wj * pick<KP>(e2, n - 2) / en_last;
+        if (direct) pij = w * wj * pick<KP>(e2, n - 2) / en_last;
       }
-      if (lane < gmax) row[j] = (float)v;
+      if (lane < gmax) col[(int64_t)j * gmax] = (float)pij;
     }
   }
 }
