@@ -13,10 +13,17 @@
 // conflict-free); lane i then walks j = 0..G-1 in order and adds
 // (r_i - r_j) / rho_ij for every observed edge, dividing only when both
 // endpoints completed (rho may be 0 on edges that were never observable).
+// Bound by latency, one wave's chain per prompt.  So loads of rho, from memory and from LDS,
+// are issued kStage and kFold at a time without a condition around them (a
+// guarded load waits for its turn): positions past the block repeat its last row or column.
+// B = 512, G in 2..64: 29-33 us with a guarded load and a 64-bit division per element, 19 us so.
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace pair {
+
+constexpr int kStage = 16;   // rho loads in flight per lane
+constexpr int kFold = 8;     // partners' rho read from LDS ahead of the fold
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -38,10 +45,24 @@ __global__ __launch_bounds__(64) void edge_coeffs_kernel(
   const int stride = gmax + 1;
 
   if (pi != nullptr) {
+    // 2^lg >= g lanes to a row, kWave >> lg rows at a time.
     const float* blk = pi + b * (int64_t)gmax * gmax;
-    for (int64_t idx = lane; idx < g * g; idx += kWave) {
-      const int64_t i = idx / g, j = idx - i * g;
-      rho_lds[i * stride + j] = blk[i * gmax + j];
+    const int n = (int)g;
+    const int lg = 32 - __clz(n - 1);
+    const int col = (lane & ((1 << lg) - 1)) < n ? (lane & ((1 << lg) - 1)) : n - 1;
+    const int rows = kWave >> lg;
+    for (int i0 = lane >> lg; i0 < n; i0 += rows * kStage) {
+      float v[kStage];
+#pragma unroll
+      for (int s = 0; s < kStage; ++s) {
+        const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
+        v[s] = blk[i * gmax + col];
+      }
+#pragma unroll
+      for (int s = 0; s < kStage; ++s) {
+        const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
+        rho_lds[i * stride + col] = v[s];
+      }
     }
   }
   __syncthreads();
@@ -55,25 +76,35 @@ __global__ __launch_bounds__(64) void edge_coeffs_kernel(
 
   float c = 0.0f, nsn = 0.0f, sw = 0.0f, sw2 = 0.0f, wmx = 0.0f;
   bool bad_rho = false;
-  for (int j = 0; j < g; ++j) {
-    const float r_j = lane_value(r_i, j);
-    if (!((obs >> j) & 1ull) || !m_i || j == lane) continue;
-    float rho = 1.0f, pij = 1.0f;
-    if (pi != nullptr) {
-      const int lo = lane < j ? lane : j, hi = lane < j ? j : lane;
-      rho = rho_lds[lo * stride + hi];
-      pij = rho_lds[j * stride + j];
+  for (int j0 = 0; j0 < g; j0 += kFold) {
+    float rho[kFold], pij[kFold];
+#pragma unroll
+    for (int s = 0; s < kFold; ++s) {
+      rho[s] = pij[s] = 1.0f;
+      if (pi != nullptr) {
+        const int j = j0 + s < g ? j0 + s : (int)g - 1;
+        const int i = vert ? lane : 0;
+        const int lo = i < j ? i : j, hi = i < j ? j : i;
+        rho[s] = rho_lds[lo * stride + hi];
+        pij[s] = rho_lds[j * stride + j];
+      }
     }
-    float term, we, ir;
-    if (!rule_term(rule, wmax, r_i - r_j, rho, pii, pij, &term, &we, &ir)) {
-      bad_rho = true;
-      continue;
+#pragma unroll
+    for (int s = 0; s < kFold; ++s) {
+      const int j = j0 + s;
+      const float r_j = lane_value(r_i, j < kWave ? j : 0);
+      if (j >= g || !((obs >> j) & 1ull) || !m_i || j == lane) continue;
+      float term, we, ir;
+      if (!rule_term(rule, wmax, r_i - r_j, rho[s], pii, pij[s], &term, &we, &ir)) {
+        bad_rho = true;
+        continue;
+      }
+      c += term;
+      nsn += ir;
+      sw += we;
+      sw2 += we * we;
+      wmx = fmaxf(wmx, we);
     }
-    c += term;
-    nsn += ir;
-    sw += we;
-    sw2 += we * we;
-    wmx = fmaxf(wmx, we);
   }
   if (bad_rho) raise_status(d_status, PAIR_ST_RHO_RANGE);
 
@@ -104,7 +135,7 @@ __global__ __launch_bounds__(64) void edge_coeffs_kernel(
 
 // Design draw and HT coefficient fold of one replicate in one launch: one
 // wavefront per prompt, lane i = vertex i.  The indicators are drawn exactly
-// as design_draw_kernel draws them, the logged rho_ij = fl32(p_i p_j) is
+// as design_wave_kernel draws them, the logged rho_ij = fl32(p_i p_j) is
 // formed on the fly (the value the design writes to its pi block), and the
 // fold adds (r_i - r_j) / rho_ij over observed partners in ascending order,
 // then centres -- the same arithmetic as edge_coeffs_kernel on the logged
