@@ -141,7 +141,7 @@ def _dev(t, name, dtype, numel=None, allow_none=False):
         if allow_none:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
@@ -149,16 +149,15 @@ def _dev(t, name, dtype, numel=None, allow_none=False):
         raise ValueError(f"{name} must be contiguous")
     if numel is not None and t.numel() < numel:
         raise ValueError(f"{name} holds {t.numel()} elements, needs {numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()   # the declared argument type makes the pointer
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _scores_arg(scores):
-    if not isinstance(scores, torch.Tensor) or scores.device.type != "cuda" or scores.dim() != 2:
+    if not isinstance(scores, torch.Tensor) or not scores.is_cuda or scores.dim() != 2:
         raise ValueError("scores must be a 2-D CUDA tensor [nv][ld-strided rows]")
     if scores.stride(1) != 1:
         raise ValueError("scores rows must be contiguous")
@@ -168,7 +167,7 @@ def _scores_arg(scores):
         code = PAIR_BF16
     else:
         raise TypeError("scores must be float32 or bfloat16")
-    return ctypes.c_void_p(scores.data_ptr()), code, scores.stride(0), scores.shape[1]
+    return scores.data_ptr(), code, scores.stride(0), scores.shape[1]
 
 
 def _rc(code, where):
@@ -371,11 +370,13 @@ def _allocating(fn):
     """Run an allocating helper with its `stream` argument (when given) as
     torch's current stream: outputs, status words and temporary workspaces
     are then allocated and zero-filled on the stream the kernels run on."""
-    sig = inspect.signature(fn)
+    # `stream` is found by its place: binding the signature on each call took
+    # longer than a small batch's kernels.
+    at = list(inspect.signature(fn).parameters).index("stream")
 
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
-        stream = sig.bind(*args, **kwargs).arguments.get("stream")
+        stream = args[at] if len(args) > at else kwargs.get("stream")
         if stream is None:
             return fn(*args, **kwargs)
         with torch.cuda.stream(stream):
