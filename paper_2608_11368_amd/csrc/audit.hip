@@ -465,12 +465,19 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
   for (int idx = 4 * tid; idx < KP * KP; idx += 4 * kEvalThreads)
     *reinterpret_cast<float4*>(Ws + idx) =
         *reinterpret_cast<const float4*>(wt + b * (KP * KP) + idx);
-  const bool live = COS || flag[b] != 0;
+  const bool live = flag[b] != 0;
   int64_t o0, g64;
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
   const int g = (int)g64;
   const int nb = KS == 1 ? 1 : (g + 15) / 16;
   const uint64_t group = g == 64 ? ~0ull : (1ull << g) - 1ull;   // bits the draws wrote
+  if (COS && !live) {   // equal rewards: a = 0, no direction to compare with
+    if (tid == 0) {
+      epart[b * nchunk + chunk] = 0.0;
+      if (chunk == 0) target_norm[b] = 0.0;
+    }
+    return;
+  }
   if (!live) {   // equal rewards: every delta_r is exactly 0
     for (int t = 0; t < rounds; ++t) {
       const int64_t r = first + t * kWave + lane;
