@@ -42,6 +42,7 @@ namespace pair {
 
 namespace {
 
+constexpr int kManyClose = 32;     // see the joint block
 constexpr int kMaxFitIter = 200;   // evaluations of pi(w), rejected steps included
 
 // e_0..e_{KP-1} (only k <= n meaningful) of the units 0..g-1 excluding skip1
@@ -61,6 +62,16 @@ __device__ __forceinline__ void esp_excl(double w, int g, int n, int skip1, int 
   }
 }
 
+// e_k of the units but two, in lane k.
+__device__ __forceinline__ double esp_excl_wave(double w, int g, int lane, int skip1, int skip2) {
+  double e = lane == 0 ? 1.0 : 0.0;
+  for (int m = 0; m < g; ++m) {
+    const double wm = (m == skip1 || m == skip2) ? 0.0 : readlane_d(w, m);
+    e = __dadd_rn(e, __dmul_rn(wm, dpp_d<0x138>(e)));   // wave_shr:1
+  }
+  return e;
+}
+
 // e[k] for a run-time k, by an unrolled select (keeps e in registers).
 template <int KP>
 __device__ __forceinline__ double pick(const double (&e)[KP], int k) {
@@ -71,8 +82,8 @@ __device__ __forceinline__ double pick(const double (&e)[KP], int k) {
 }
 
 // Prefix rows Pf[m][k] = e_k(w_0 .. w_{m-1}), m = 0..g, and suffix rows
-// Sf[m][k] = e_k(w_{m+1} .. w_{g-1}), m = 0..g-1, for k <= n, written to LDS
-// with row stride kS.  Lane k carries coefficient k; adding unit m is
+// Sf[m][k] = e_k(w_{m+1} .. w_{g-1}), m = 0..g-1, written to LDS with row
+// stride kS (only k <= n is read).  Lane k carries coefficient k; adding unit m is
 // e_k <- e_k + w_m e_{k-1}, where e_{k-1} arrives from lane k - 1 by a
 // whole-wave DPP shift (lane 0 receives 0).
 constexpr int kS = 65;
@@ -82,20 +93,18 @@ __device__ __forceinline__ void esp_tables(double w, int g, int n, int lane, dou
                                            double* Sf) {
   // The two serial chains run side by side.
   double pre = lane == 0 ? 1.0 : 0.0, suf = pre;
-  if (lane <= n) {
-    Pf[lane] = pre;
-    Sf[(g - 1) * kS + lane] = suf;
-  }
-  for (int m = 0; m < g; ++m) {
+  Pf[lane] = pre;
+  Sf[(g - 1) * kS + lane] = suf;
+  for (int m = 0; m < g - 1; ++m) {
     const int u = g - 1 - m;
     const double wp = readlane_d(w, m), ws = readlane_d(w, u);
     pre = __dadd_rn(pre, __dmul_rn(wp, dpp_d<0x138>(pre)));   // wave_shr:1
     suf = __dadd_rn(suf, __dmul_rn(ws, dpp_d<0x138>(suf)));
-    if (lane <= n) {
-      Pf[(m + 1) * kS + lane] = pre;
-      if (u >= 1) Sf[(u - 1) * kS + lane] = suf;
-    }
+    Pf[(m + 1) * kS + lane] = pre;
+    Sf[(u - 1) * kS + lane] = suf;
   }
+  pre = __dadd_rn(pre, __dmul_rn(readlane_d(w, g - 1), dpp_d<0x138>(pre)));
+  Pf[g * kS + lane] = pre;
   __syncthreads();
 }
 
@@ -106,54 +115,58 @@ __device__ __forceinline__ double recip_d(double x) {
   return fma(r, fma(e, e, e), r);
 }
 
-// Step K and all after it of the elimination of the Newton system, without
-// pivoting (the matrix is symmetric positive definite).  Lane i owns row i.  Every other
+// Eight steps of the elimination of the Newton system, without pivoting (the
+// matrix is symmetric positive definite), on the pivots k0 .. k0 + 7.  Lane i
+// owns row i, shifted left by k0, of which W entries are left.  Every other
 // row is cleared of the pivot column, rows above included (Gauss-Jordan: the
-// lanes run anyway, and no back substitution is left).  The rows and columns from the pivot on
-// stay symmetric, so the pivot row is the pivot column: one store of a[K] by
-// all lanes, read back as broadcasts, kChunk entries in flight while the last
-// ones are used.  The steps are unrolled, so that register indices are constants
-// and no row moves.  One wave, whose LDS accesses keep their order: no waits
-// but for the data.
+// lanes run anyway, and no back substitution is left).  The rows and columns
+// from the pivot on stay symmetric, so the pivot row is the pivot column: one
+// store of it by all lanes, read back as broadcasts, kChunk entries in flight
+// while the last ones are used.  One wave, whose LDS accesses keep their order:
+// no waits but for the data.  Eight steps are unrolled, so that register indices
+// are constants; all 64 took 55 KB of code and the same time.
 constexpr int kChunk = 16;
+constexpr int kPivots = 8;
 
-template <int KP, int K>
-__device__ __forceinline__ void eliminate(int g, int lane, double (&a)[KP], double& x,
+template <int KP, int W>
+__device__ __forceinline__ void eliminate(int k0, int lane, double (&a)[KP], double& x,
                                           double& inv_piv, double* buf) {
-  if (K >= g) return;
-  double* v = buf + (K & 1) * kWave;
-  v[lane] = a[K];
-  __builtin_amdgcn_wave_barrier();
-  constexpr int C0 = (K + 1) & ~1;   // pairs of entries, 16 bytes a load
-  constexpr int N = (KP - C0 + kChunk - 1) / kChunk;
-  double u[2][kChunk];
 #pragma unroll
-  for (int e = 0; e < kChunk; ++e)
-    if (C0 + e < KP) u[0][e] = v[C0 + e];
-  __builtin_amdgcn_sched_barrier(0);
-  const double inv = recip_d(readlane_d(a[K], K));
-  const double xk = readlane_d(x, K);
-  const double m = lane == K ? 0.0 : a[K] * inv;
-  inv_piv = lane == K ? inv : inv_piv;
-  x = fma(-m, xk, x);
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
+  for (int s = 0; s < kPivots; ++s) {
+    double* v = buf + (s & 1) * (2 * kWave);   // upper half zero: columns past the wave
+    v[lane] = a[s];
+    __builtin_amdgcn_wave_barrier();
+    const double* vk = v + k0;
+    const int c0 = (s + 1) & ~1;   // pairs of entries, 16 bytes a load
+    const int n = (W - c0 + kChunk - 1) / kChunk;
+    double u[2][kChunk];
 #pragma unroll
     for (int e = 0; e < kChunk; ++e)
-      if (C0 + (c + 1) * kChunk + e < KP) u[(c + 1) & 1][e] = v[C0 + (c + 1) * kChunk + e];
+      if (c0 + e < W) u[0][e] = vk[c0 + e];
     __builtin_amdgcn_sched_barrier(0);
+    const double inv = recip_d(readlane_d(a[s], k0 + s));
+    const double xk = readlane_d(x, k0 + s);
+    const bool pivot = lane == k0 + s;
+    const double m = pivot ? 0.0 : a[s] * inv;
+    inv_piv = pivot ? inv : inv_piv;
+    x = fma(-m, xk, x);
 #pragma unroll
-    for (int e = 0; e < kChunk; ++e) {
-      const int j = C0 + c * kChunk + e;
-      if (j > K && j < KP) {
-        a[j] = fma(-m, u[c & 1][e], a[j]);
-        // used here: left to itself the compiler moves the sum behind the
-        // next step's exit and keeps its operands, which spills
-        asm volatile("" : "+v"(a[j]));
+    for (int c = 0; c < n; ++c) {
+#pragma unroll
+      for (int e = 0; e < kChunk; ++e) {
+        const int j = c0 + (c + 1) * kChunk + e;
+        if (j < W) u[(c + 1) & 1][e] = vk[j];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < kChunk; ++e) {
+        const int j = c0 + c * kChunk + e;
+        if (j > s && j < W) a[j] = fma(-m, u[c & 1][e], a[j]);
       }
     }
   }
-  if constexpr (K + 1 < KP) eliminate<KP, K + 1>(g, lane, a, x, inv_piv, buf);
+#pragma unroll
+  for (int j = 0; j < W; ++j) a[j] = j + kPivots < W ? a[j + kPivots] : 0.0;
 }
 
 template <int KP>
@@ -216,8 +229,19 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
     pi = 0.0;
     if (unit) {
       double e1 = 0.0;   // e_{n-1}(w without i) = sum_k Pf[i][k] Sf[i][n-1-k]
-      for (int k = 0; k < n; ++k)
-        e1 = __dadd_rn(e1, __dmul_rn(Pf[lane * kS + k], Sf[lane * kS + (n - 1 - k)]));
+      // eight reads of each table in flight; terms past n add 0
+      for (int k = 0; k < n; k += 8) {
+        double pk[8], sk[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const int kk = k + s < n ? k + s : n - 1;
+          pk[s] = Pf[lane * kS + kk];
+          sk[s] = Sf[lane * kS + (n - 1 - kk)];
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+          e1 = __dadd_rn(e1, k + s < n ? __dmul_rn(pk[s], sk[s]) : 0.0);
+      }
       pi = w * e1 / en;
     }
     const double f = wave_sum_d(unit ? t * th : 0.0) - log(en);
@@ -267,7 +291,8 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
         double h = pij - pi * pj + inv_g, hd = pi * (1.0 - pi) + inv_g;
         asm("" : "+v"(h), "+v"(hd));
         h = (off && sep) ? h : 0.0;
-        Pf[j * kS + lane] = (unit && j == lane) ? hd : h;
+        // the identity past the group: whole blocks of pivots are eliminated
+        Pf[j * kS + lane] = j != lane ? h : (unit ? hd : 1.0);
       }
     }
     if (__ballot(nclose > 0) != 0ull) {
@@ -278,12 +303,18 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
         if (close) Pf[j * kS + lane] = share - pi * pj + inv_g;
       }
     }
-    for (int j = (g + 3) & ~3; j < KP; ++j) Pf[j * kS + lane] = 0.0;
+    for (int j = (g + 3) & ~3; j < KP; ++j) Pf[j * kS + lane] = j == lane ? 1.0 : 0.0;
     double a[KP];   // a lane reads what it wrote
 #pragma unroll
     for (int j = 0; j < KP; ++j) a[j] = Pf[j * kS + lane];
     double x = unit ? t - pi : 0.0, inv_piv = 0.0;
-    eliminate<KP, 0>(g, lane, a, x, inv_piv, Sf);
+    Sf[kWave + lane] = Sf[3 * kWave + lane] = 0.0;
+    int k0 = 0;
+    if constexpr (KP > 32)
+      for (; k0 < g && k0 < KP - 32; k0 += kPivots) eliminate<KP, KP>(k0, lane, a, x, inv_piv, Sf);
+    if constexpr (KP > 16)
+      for (; k0 < g && k0 < KP - 16; k0 += kPivots) eliminate<KP, 32>(k0, lane, a, x, inv_piv, Sf);
+    for (; k0 < g; k0 += kPivots) eliminate<KP, 16>(k0, lane, a, x, inv_piv, Sf);
     x *= inv_piv;
     d = unit ? x : 0.0;
     slope = wave_sum_d(unit ? (t - pi) * d : 0.0);
@@ -308,19 +339,32 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
     // accuracy, so it is used where the two odds differ by more than 1e-5
     // (error below 1e-8, under the fp32 output's rounding); closer pairs
     // take the leave-two-out polynomial.
+    // e_{n-2} of a few pairs is the wave's work, a lane per coefficient (the
+    // same operations in the same order, about 2,000 cycles a pair); from kManyClose
+    // pairs in a row on it is every lane's own polynomial, 65,000 cycles.
+    // Always the latter, a batch waited for the one prompt with a close pair:
+    // 235 us for 512 prompts of 2..64, where the fits take 115; now 136.
     float* col = pi_joint + b * (int64_t)gmax * gmax + lane;
     for (int j = 0; j < gmax; ++j) {
       const double wj = readlane_d(w, j < g ? j : 0), pj = readlane_d(pi, j < g ? j : 0);
       const bool pair_ij = unit && j < g && j != lane;
       const bool sep = fabs(wj - w) > 1e-5 * fmax(wj, w);
-      double pij = 0.0;
-      if (unit && j == lane) pij = pi;
-      if (pair_ij && sep) pij = (wj * pi - w * pj) / (wj - w);
+      double diff = (wj * pi - w * pj) * recip_d(wj - w);
+      asm("" : "+v"(diff));   // selected, not branched to
+      double pij = (pair_ij && sep) ? diff : 0.0;
+      pij = (unit && j == lane) ? pi : pij;
       const bool direct = pair_ij && !sep && n >= 2;
-      if (__ballot(direct) != 0ull) {
+      uint64_t close = __ballot(direct);
+      if (__popcll(close) >= kManyClose) {
         double e2[KP];
         esp_excl<KP>(w, g, n - 2, lane, j, e2);   // w of lane j is excluded too
         if (direct) pij = w * wj * pick<KP>(e2, n - 2) / en_last;
+      } else {
+        for (; close != 0ull; close &= close - 1ull) {
+          const int i = __ffsll((unsigned long long)close) - 1;
+          const double e2 = readlane_d(esp_excl_wave(w, g, lane, i, j), n - 2);
+          if (lane == i) pij = w * wj * e2 / en_last;
+        }
       }
       if (lane < gmax) col[(int64_t)j * gmax] = (float)pij;
     }
