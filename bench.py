@@ -8,14 +8,15 @@ inputs:
       launch, writing the mask and the logged rho block too) ->
       pair_weighted_grad
   estimator audit on workload audit (B=256, G=16, D=65536 bf16, R=4096):
-      pair_audit (replicate coefficients, matrix-core contraction with the
-      squared-norm epilogue, fp64 reductions)
+      pair_audit (each prompt's Gram matrix and its draws in one stream, the
+      replicates' quadratic forms, fp64 reductions)
 
 Prints ONE JSON line.  `value` is the gradient chain's throughput in GB/s of
 algorithmic bytes (score rows with a nonzero coefficient, the coefficients,
 and the fp32 output), i.e. bytes that must cross HBM, over the chain's event
 time.  The audit is reported in replicate-estimates/s and TFLOP/s (2*G*D flop
-per replicate estimate of the prompts it sweeps) in the "audit" object.
+per replicate estimate of the prompts it sweeps: those of the dense
+contraction, which the Gram form does not execute) in the "audit" object.
 "roofline" is the weighted-gradient kernel on the worst of the three gradient
 workloads (b128, the Qwen3-shaped slice, ragged), each timed with HIP events on
 the stream it is launched on; "roofline_by_config" lists all of them, per

@@ -371,21 +371,14 @@ size_t pair_audit_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R)
  *     e_r  = || g_r - t ||^2 = || (A~^(r) - a) S_b ||^2
  *     mse  = (1/R) sum_r e_r
  *     bias = || (1/R) sum_r g_r - t ||
- * The R x D estimates are never materialised: (A~^(r) - a) times S_b runs on
- * the matrix cores with the squared norm reduced in the epilogue.  Operands
- * are fp16 after power-of-two rescaling: each score row by its largest
- * magnitude within a column slice, then rounded to nearest fp16, which is
- * exact for entries within 2^17 of that maximum and off by at most 2^-25 of
- * it below; each replicate row of A~^(r) - a by its largest entry, then one
- * fp16 rounding (2^-11 relative).  With delta_r = A~^(r) - a, y_r =
- * delta_r S_b, z_r = S_b y_r^T (so e_r = delta_r . z_r) and u = 2^-11, that
- * rounding has the same relative error in every score column, so to first
- * order |Delta e_r| <= 2 u sum_i |delta_ri z_ri|, plus terms of 2^-25 of
- * the row maxima M_i for fp16 subnormals: at most 2u e_r when the terms
- * delta_ri z_ri share a sign (near-orthogonal score rows), more only when
- * they cancel, as with a single score column.  The bias row
- * (1/R) sum_r (A~^(r) - a) is applied in fp32 on the vector units, without
- * that rounding.  A replicate's e_r does not depend on R or rep0: calls over
+ * The R x D estimates are never materialised: with delta_r = A~^(r) - a and
+ * K = S_b S_b^T, e_r = delta_r K delta_r^T, and the bias is the same form of
+ * the mean row.  K is formed on the matrix cores from exact products with fp32
+ * sums of short runs, moved to fp64; the fold is fp32, the quadratic
+ * forms fp64.  So |Delta e_r| is a small multiple of 2^-24 A_r^2 with
+ * A_r = sum_i (|A~^(r)_i| + |a_i|) |s_i|: about 1e-7 of e_r unless the rows
+ * nearly cancel in delta_r S_b.  A replicate's e_r does not depend
+ * on R or rep0: calls over
  * consecutive replicate ranges return bitwise the rep_sqerr of one call over
  * their union.  Weights use rho = pi_w when given (e.g. all ones replays the
  * unweighted estimator of Prop. 1), else the logged fl32(p_i p_j).
