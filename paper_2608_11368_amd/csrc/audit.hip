@@ -11,7 +11,7 @@
 //     cos_r = <g_r, t> / (|g_r| |t|) = u_r K a / sqrt(u_r K u_r * a K a),
 // so the score rows are needed once, for K, and a replicate costs G^2
 // operations instead of 2 G D.  K is formed from exact bf16 products with
-// fp32 sums of at most a slice's columns, everything after it is fp64: e_r is
+// fp32 sums of 128 columns, everything after it but the fold is fp64: e_r is
 // within about 1e-7 of 64-bit arithmetic for score rows that do not nearly
 // cancel in delta_r S_b, and the error grows with the square of that
 // cancellation, |delta|.|s| over |delta S|.  Contracting delta_r S_b column by
@@ -48,6 +48,11 @@ constexpr int kTableThreads = 256;
 constexpr int64_t kMaxSlices = 128;   // score-column slices per prompt at most
 constexpr int64_t kDrawRun = 512;     // replicates a stream workgroup draws at most, about
 
+// Groups that may exceed 48: the fp64 sums of ten tiles leave no registers for
+// the generator beside them, so the prompt's first workgroups draw and the others
+// stream (B = 64, G in 2..64, D = 20011, R = 1000: 46 us, with both in one 54 us).
+__host__ __device__ constexpr bool draws_apart(int ks) { return ks == 4; }
+
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -55,7 +60,7 @@ struct AuditLayout {
   int ks, kp;
   int64_t nsl;     // score-column slices per prompt
   int64_t slice;   // columns per slice
-  int64_t slots;   // audit_stream workgroups per prompt: nsl slices, and more if R is large
+  int64_t slots;   // audit_stream workgroups per prompt: nsl slices, and those that only draw
   int64_t nchunk;  // audit_eval workgroups per prompt
   int rounds;      // and times 64 replicates each of their waves takes
   size_t part_off, gex_off, k_off, w_off, v_off, a_off, flag_off, bits_off, epart_off, dpart_off,
@@ -74,7 +79,10 @@ AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   if (nsl > kMaxSlices) nsl = kMaxSlices;
   L.slice = round_up(ceil_div(D, nsl), kGramRoundCols);
   L.nsl = ceil_div(D, L.slice);
-  L.slots = L.nsl > ceil_div(R, kDrawRun) ? L.nsl : ceil_div(R, kDrawRun);
+  if (draws_apart(L.ks))
+    L.slots = L.nsl + ceil_div(R, kDrawRun);
+  else
+    L.slots = L.nsl > ceil_div(R, kDrawRun) ? L.nsl : ceil_div(R, kDrawRun);
   // A wave's first 64 replicates cost the latency of its tables, so with many
   // it takes twice 64 (28.5 us against 26.4 us at B = 256, G = 16, R = 4096;
   // four times: 28.1 us, the last workgroups run alone).  Groups above 32 have
@@ -88,7 +96,7 @@ AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
     off += (size_t)round_up(bytes, 256);
     return at;
   };
-  L.part_off = take(B * L.nsl * gram_tiles(L.ks) * 256 * 4);   // slice partials of K
+  L.part_off = take(B * L.nsl * gram_tiles(L.ks) * 256 * 8);   // slice partials of K
   L.gex_off = take(B * L.nsl * (L.kp + 1) * 4);                // their row exponents
   L.k_off = take(B * L.kp * L.kp * 8);                         // K, fp64
   L.w_off = take(B * L.kp * L.kp * 4);                         // edge table
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void audit_stream
     int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t D,
     const uint16_t* __restrict__ scores, int64_t ld, int nsl, int64_t slice, int slots,
     const float* __restrict__ rewards, const float* __restrict__ p, uint64_t seed, int64_t rep0,
-    int64_t pbase, int64_t R, int skip_equal, int rescale, float* __restrict__ part,
+    int64_t pbase, int64_t R, int skip_equal, int rescale, double* __restrict__ part,
     int32_t* __restrict__ gex, uint16_t* __restrict__ bits, int want_counts, int32_t* d_status) {
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
@@ -156,11 +164,13 @@ __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void audit_stream
   __syncthreads();
 
   // This wave's draws: items of 64 replicates (lane = replicate) and 16
-  // vertices, dealt to the prompt's waves in turn.  One unit is one Philox
+  // vertices, dealt to the prompt's drawing waves in turn.  One unit is one Philox
   // block (four vertices) of one item; an item is 16 bits of the word.
+  const int drawers = draws_apart(KS) ? slots - nsl : slots;
+  const int slice_at = draws_apart(KS) ? slot - drawers : slot;
   const int ngrp = (g + 15) / 16;
-  const int stride = slots * kGramWaves;
-  const int nitems = (int)((R + kWave - 1) / kWave) * ngrp;
+  const int stride = drawers * kGramWaves;
+  const int nitems = slot < drawers ? (int)((R + kWave - 1) / kWave) * ngrp : 0;
   int item = slot * kGramWaves + wave;
   const int units = item < nitems ? 4 * ((nitems - item + stride - 1) / stride) : 0;
   int done = 0;
@@ -190,16 +200,17 @@ __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void audit_stream
       }
     }
   };
-  if (wanted && slot < nsl) {
-    const int64_t c_lo = slot * slice;
+  if (wanted && slice_at >= 0 && slice_at < nsl) {
+    const int64_t c_lo = slice_at * slice;
     const int64_t c_hi = c_lo + slice < D ? c_lo + slice : D;
-    gram_slice_of<KS, false>(
-        scores + o0 * ld, ld, g, c_lo, c_hi, stage, ex, rescale != 0,
-                      part + (b * nsl + slot) * (kTiles * 256),
-                      gex + (b * nsl + slot) * (KP + 1), d_status, [&](int k, int n) {
+    gram_slice_of<KS>(scores + o0 * ld, ld, g, c_lo, c_hi, stage, ex, rescale != 0,
+                      part + (b * nsl + slice_at) * (kTiles * 256),
+                      gex + (b * nsl + slice_at) * (KP + 1), d_status, [&](int k, int n) {
+                        if (draws_apart(KS)) return;
                         draw_until(k + 1 < n ? (int)((float)units * (float)(k + 1) / (float)n)
                                              : units);
                       });
+    if (draws_apart(KS)) return;
   }
   draw_until(units);
 }
@@ -234,7 +245,7 @@ template <int KS>
 __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
     int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
     const float* __restrict__ rewards, const float* __restrict__ p, const float* __restrict__ pi_w,
-    int32_t rule, float wmax, int64_t nsl, int skip_equal, const float* __restrict__ part,
+    int32_t rule, float wmax, int64_t nsl, int skip_equal, const double* __restrict__ part,
     const int32_t* __restrict__ gex, double* __restrict__ K, float* __restrict__ wt,
     float* __restrict__ vt, double* __restrict__ a_out, int32_t* __restrict__ flag,
     int32_t* d_status) {
@@ -263,14 +274,14 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
           c = y;
         }
     const int i = 16 * a + 4 * (tid >> 6) + (tid & 3), j = 16 * c + ((tid >> 2) & 15);
-    const float* src = part + (b * nsl * kTiles + t) * 256 + tid;
+    const double* src = part + (b * nsl * kTiles + t) * 256 + tid;
     const int32_t* gx = gex + b * nsl * (KP + 1);
     double k = 0.0;
     const bool inside = 16 * c < g;   // uniform; entries past g inside a block are 0
     // Loads past the last slice repeat it (a guarded load would wait for its
     // turn) and are not added.
     for (int64_t s0 = 0; inside && s0 < nsl; s0 += 16) {
-      float v[16];
+      double v[16];
       int32_t scaled[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
@@ -281,7 +292,7 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         if (s0 + q >= nsl) break;
-        double x = (double)v[q];
+        double x = v[q];
         if (skip_equal && scaled[q] != 0) {   // else the exponents were not written
           const int32_t* row = gx + (s0 + q) * (KP + 1);
           // rows past the prompt's own blocks have no exponent
@@ -785,7 +796,7 @@ struct AuditArgs {
 template <int KS, bool COS>
 int run_audit(const AuditLayout& L, const AuditArgs& A) {
   unsigned char* ws = static_cast<unsigned char*>(A.workspace);
-  float* part = reinterpret_cast<float*>(ws + L.part_off);
+  double* part = reinterpret_cast<double*>(ws + L.part_off);
   int32_t* gex = reinterpret_cast<int32_t*>(ws + L.gex_off);
   double* K = reinterpret_cast<double*>(ws + L.k_off);
   float* wt = reinterpret_cast<float*>(ws + L.w_off);

@@ -16,7 +16,7 @@
 // matrix cores plus O(G^3) fp64 work:
 //
 //  1. gram_kernel    workgroup = (prompt, column slice): the slice's partial
-//                    Gram matrix in fp32 (gram.hpp), bound by HBM.
+//                    Gram matrix (gram.hpp), bound by HBM.
 //  2. exact_final_kernel  workgroup per prompt: K in fp64 (slices summed in
 //                    order), the rule's coefficients, beta^T K beta and the
 //                    covariance trace with a fixed-order reduction.  The
@@ -43,6 +43,7 @@ struct ExactLayout {
   int ks, kp;
   int64_t nsl;     // column slices per prompt
   int64_t slice;   // columns per slice (whole rounds of a workgroup's waves)
+  bool wide;       // slice partials in fp64
   size_t total;
 };
 
@@ -50,11 +51,12 @@ ExactLayout exact_layout(int64_t B, int32_t gmax, int64_t D) {
   ExactLayout L;
   L.ks = (gmax + 15) / 16;
   L.kp = 16 * L.ks;
-  // Slices of 2048 columns (64 KB per 16 rows), longer ones where a group of 16
-  // or 32 may be the batch's largest and while 1024 workgroups remain; at most
-  // about 8192 workgroups over the batch.
+  // Slices of 4096 columns, 8192 for groups of at most 16, while 1024
+  // workgroups remain (at B = 128, G in 2..64, D = 65536 their partials take the
+  // two kernels 130 us with 2048 columns and 121 us with 4096), else 2048; at
+  // most about 8192 workgroups over the batch.
   const int64_t round = kGramRoundCols;
-  const int64_t longer = L.ks == 1 ? 4 : (L.ks == 2 ? 2 : 1);
+  const int64_t longer = L.ks == 1 ? 4 : 2;
   int64_t nsl = ceil_div(D, longer * round);
   if (B * nsl < 1024) {
     nsl = ceil_div(1024, B);
@@ -69,16 +71,20 @@ ExactLayout exact_layout(int64_t B, int32_t gmax, int64_t D) {
   int64_t old = ceil_div(8192, B);
   if (old > ceil_div(D, 512)) old = ceil_div(D, 512);
   old = ceil_div(D, ceil_div(ceil_div(D, old), 512) * 512);
+  // fp64 partials where that size holds them, which is all but rows of fewer than
+  // 1024 columns and batches of thousands of prompts; else fp32, a rounding of
+  // 2^-25 per slice.
   const int64_t now = L.nsl * gram_tiles(L.ks) * 256;
+  L.wide = 2 * now <= old * L.kp * L.kp;
   L.total = (size_t)B * (size_t)(old * L.kp * L.kp > now ? old * L.kp * L.kp : now) * sizeof(float);
   return L;
 }
 
-template <int KS>
+template <int KS, class Part>
 __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void gram_kernel(
     int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int64_t D,
     const uint16_t* __restrict__ scores, int64_t ld, int64_t nsl, int64_t slice,
-    float* __restrict__ part) {
+    Part* __restrict__ part) {
   __shared__ __align__(16) uint16_t stage[gram_lds_elems(KS)];
   const int64_t b = blockIdx.x / nsl;
   const int64_t sl = blockIdx.x - b * nsl;
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void gram_kernel(
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, nullptr, false)) return;
   const int64_t c_lo = sl * slice;
   const int64_t c_hi = c_lo + slice < D ? c_lo + slice : D;
-  gram_slice_of<KS, true>(scores + o0 * ld, ld, (int)g, c_lo, c_hi, stage, nullptr, false,
+  gram_slice_of<KS>(scores + o0 * ld, ld, (int)g, c_lo, c_hi, stage, nullptr, false,
                     part + (b * nsl + sl) * (gram_tiles(KS) * 256), nullptr, nullptr,
                     [](int, int) {});
 }
@@ -103,12 +109,12 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return t;
 }
 
-template <int KS>
+template <int KS, class Part>
 __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
     int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
     const float* __restrict__ rewards, const float* __restrict__ p,
     const float* __restrict__ pi_w, int32_t rule, float wmax, int64_t nsl,
-    const float* __restrict__ part, double* __restrict__ mse, double* __restrict__ bias_norm,
+    const Part* __restrict__ part, double* __restrict__ mse, double* __restrict__ bias_norm,
     double* __restrict__ gram, int32_t* d_status) {
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
@@ -138,11 +144,11 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   double sum[kOwn];
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) sum[u] = 0.0;
-  const float* src = part + b * nsl * (kTiles * 256) + e;
+  const Part* src = part + b * nsl * (kTiles * 256) + e;
   // Loads past the last slice or tile repeat it (a guarded load would wait for
   // its turn) and are not added.
   for (int64_t s0 = 0; s0 < nsl; s0 += 8) {
-    float v[kOwn][8];
+    Part v[kOwn][8];
 #pragma unroll
     for (int u = 0; u < kOwn; ++u) {
       int t = tid / 256 + u * (kFinalThreads / 256);
@@ -297,30 +303,33 @@ int launch_audit_exact(int64_t B, int64_t nv, int32_t gmax, const int64_t* offse
                        double* bias_norm, double* gram, void* workspace, int32_t* d_status,
                        hipStream_t stream) {
   const ExactLayout L = exact_layout(B, gmax, D);
-  float* part = static_cast<float*>(workspace);
   const uint16_t* s = static_cast<const uint16_t*>(scores);
   const int64_t grid = B * L.nsl;
   if (grid > 0x7fffffffLL) return PAIR_ERANGE;
-#define PAIR_GRAM(KS_)                                                                         \
-  hipLaunchKernelGGL(gram_kernel<KS_>, dim3((unsigned)grid), dim3(kGramThreads), 0, stream, nv, \
-                     gmax, offsets, D, s, ld, L.nsl, L.slice, part)
-#define PAIR_FINAL(KS_)                                                                     \
-  hipLaunchKernelGGL(exact_final_kernel<KS_>, dim3((unsigned)B), dim3(kFinalThreads), 0,    \
-                     stream, B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, L.nsl, part, \
-                     mse, bias_norm, gram, d_status)
+#define PAIR_GRAM(KS_, PART_)                                                                    \
+  hipLaunchKernelGGL((gram_kernel<KS_, PART_>), dim3((unsigned)grid), dim3(kGramThreads), 0,      \
+                     stream, nv, gmax, offsets, D, s, ld, L.nsl, L.slice,                        \
+                     static_cast<PART_*>(workspace))
+#define PAIR_FINAL(KS_, PART_)                                                                   \
+  hipLaunchKernelGGL((exact_final_kernel<KS_, PART_>), dim3((unsigned)B), dim3(kFinalThreads), 0, \
+                     stream, B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, L.nsl,          \
+                     static_cast<const PART_*>(workspace), mse, bias_norm, gram, d_status)
+#define PAIR_OF(LAUNCH_, KS_) \
+  if (L.wide) LAUNCH_(KS_, double); else LAUNCH_(KS_, float)
   switch (L.ks) {
-    case 1: PAIR_GRAM(1); break;
-    case 2: PAIR_GRAM(2); break;
-    case 3: PAIR_GRAM(3); break;
-    default: PAIR_GRAM(4); break;
+    case 1: PAIR_OF(PAIR_GRAM, 1); break;
+    case 2: PAIR_OF(PAIR_GRAM, 2); break;
+    case 3: PAIR_OF(PAIR_GRAM, 3); break;
+    default: PAIR_OF(PAIR_GRAM, 4); break;
   }
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
   switch (L.ks) {
-    case 1: PAIR_FINAL(1); break;
-    case 2: PAIR_FINAL(2); break;
-    case 3: PAIR_FINAL(3); break;
-    default: PAIR_FINAL(4); break;
+    case 1: PAIR_OF(PAIR_FINAL, 1); break;
+    case 2: PAIR_OF(PAIR_FINAL, 2); break;
+    case 3: PAIR_OF(PAIR_FINAL, 3); break;
+    default: PAIR_OF(PAIR_FINAL, 4); break;
   }
+#undef PAIR_OF
 #undef PAIR_GRAM
 #undef PAIR_FINAL
   return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;

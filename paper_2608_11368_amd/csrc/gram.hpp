@@ -17,8 +17,6 @@
 // chunks too.
 #pragma once
 
-#include <type_traits>
-
 #include "common.hpp"
 
 namespace pair {
@@ -78,23 +76,22 @@ __device__ __forceinline__ uint32_t scale_bf16_pair(uint32_t w, int ne) {
 // into the same registers, the compiler waits for the loads where the paths
 // meet, and nothing is in flight during the multiplication.
 //
-// With WIDE, the sums of every four matrix instructions move to fp64 (their
-// accumulation rounds with a bias, which grows with the length of a run: runs
-// of 16 left 4e-8 in the exact audit's MSE, B = 128, G in 2..64, D = 65536);
-// otherwise the fp32 accumulators run over the whole slice, 16 instructions
-// per wave and 2048 columns of 64 rows.
-template <int KS, bool HALF, bool WIDE>
+// The sums of every four matrix instructions move to fp64: their accumulation
+// rounds with a bias, which grows with the length of a run (runs of 16 left
+// 4e-8 in the exact audit's MSE, B = 128, G in 2..64, D = 65536; runs of 64, at
+// G = 64 and D = 2^20, 4e-6 in the target norm of rows that share ten parts in
+// eleven, where these leave 1e-7).
+template <int KS, bool HALF>
 struct GramAcc {
-  static constexpr bool kWide = WIDE;
   f32x4_t f[GramShape<KS, HALF>::kTiles];
-  double d[kWide ? GramShape<KS, HALF>::kTiles : 1][4];
+  double d[GramShape<KS, HALF>::kTiles][4];
 };
 
-template <int KS, bool HALF, bool WIDE, class Between>
+template <int KS, bool HALF, class Between>
 __device__ __forceinline__ void gram_pass(const uint16_t* __restrict__ rows, int64_t ld, int g,
                                           int64_t c_lo, int64_t c_hi, uint16_t* stage, int wave,
                                           int lane, bool scaled, const int32_t* ex,
-                                          GramAcc<KS, HALF, WIDE>& acc, Between&& between) {
+                                          GramAcc<KS, HALF>& acc, Between&& between) {
   using H = GramShape<KS, HALF>;
   const int rsub = lane / H::kRowLanes, csub = 8 * (lane % H::kRowLanes);
   const int64_t nwhole = (c_hi - c_lo) / H::kCols;                       // whole chunks
@@ -134,11 +131,11 @@ __device__ __forceinline__ void gram_pass(const uint16_t* __restrict__ rows, int
         for (int c = a; c < KS; ++c)
           acc.f[gram_tile(KS, a, c)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               fr[a], fr[c], acc.f[gram_tile(KS, a, c)], 0, 0, 0);
-      if (WIDE && s % 4 == 3) {
+      if (s % 4 == 3) {
 #pragma unroll
         for (int i = 0; i < H::kTiles; ++i) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc.d[WIDE ? i : 0][v] += (double)acc.f[i][v];
+          for (int v = 0; v < 4; ++v) acc.d[i][v] += (double)acc.f[i][v];
           acc.f[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
       }
@@ -217,31 +214,33 @@ __device__ __forceinline__ uint32_t row_magnitude(const uint16_t* __restrict__ r
 
 // The slice partial of one workgroup, written to part[tile][256] (tiles
 // numbered for KM row blocks, those past the prompt's KS not written) in the
-// order of gram_entry(), the waves (fp32 sums above 32
-// rows) added in order in fp64.  With `rescale`, a
+// order of gram_entry(), the waves added in order in fp64, as many tiles at a
+// time as the stage holds.  Part is double, or float where a caller's buffer
+// has room for no more.  With `rescale`, a
 // slice in which fp32 products could overflow or vanish (a row that is not
 // all zero and whose sum of squares is below 2^-80, above 2^120 or not finite) is
 // passed over again with every row divided by a power of two that brings its
 // largest magnitude into [1, 2); gex[16 KM] is then 1 and gex[0 .. 16 KM) holds
 // the exponents (gex[16 KM] is 0 otherwise), and a row that holds an infinity
 // or NaN raises PAIR_ST_NONFINITE.
-template <int KM, int KS, bool WIDE, class Between>
+template <int KM, int KS, class Part, class Between>
 __device__ __forceinline__ void gram_slice(const uint16_t* __restrict__ rows, int64_t ld, int g,
                                            int64_t c_lo, int64_t c_hi, uint16_t* stage_all,
-                                           int32_t* ex, bool rescale, float* __restrict__ part,
+                                           int32_t* ex, bool rescale, Part* __restrict__ part,
                                            int32_t* __restrict__ gex, int32_t* d_status,
                                            Between&& between) {
   constexpr bool HALF = KM <= 2;
   using H = GramShape<KS, HALF>;
-  using Sum = typename std::conditional<WIDE && KS <= 2, double, float>::type;
-  static_assert(kGramWaves * H::kTiles * 256 * sizeof(Sum) <= GramShape<KS, HALF>::kLdsElems * 2,
-                "the wave sums reuse the stage");
+  // Tiles whose wave sums fit the stage together.
+  constexpr int kFit = H::kLdsElems * (int)sizeof(uint16_t) / (kGramWaves * 256 * (int)sizeof(double));
+  constexpr int kRounds = (H::kTiles + kFit - 1) / kFit;
+  constexpr int kSumTiles = (H::kTiles + kRounds - 1) / kRounds;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   uint16_t* stage = stage_all + wave * H::kWaveElems;
-  Sum* sums = reinterpret_cast<Sum*>(stage_all);   // [wave][tile][256], after the last chunk
-  GramAcc<KS, HALF, WIDE> acc;
-  float tot[H::kTiles];
+  double* sums = reinterpret_cast<double*>(stage_all);   // [wave][tile][256], after the last chunk
+  GramAcc<KS, HALF> acc;
+  double tot[H::kTiles];
   bool again = false;
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {
@@ -249,23 +248,25 @@ __device__ __forceinline__ void gram_slice(const uint16_t* __restrict__ rows, in
     for (int i = 0; i < H::kTiles; ++i) {
       acc.f[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc.d[WIDE ? i : 0][v] = 0.0;
+      for (int v = 0; v < 4; ++v) acc.d[i][v] = 0.0;
     }
-    gram_pass<KS, HALF, WIDE>(rows, ld, g, c_lo, c_hi, stage, wave, lane, pass == 1, ex, acc, between);
-    __syncthreads();   // every wave is done with the stage
+    gram_pass<KS, HALF>(rows, ld, g, c_lo, c_hi, stage, wave, lane, pass == 1, ex, acc, between);
 #pragma unroll
-    for (int i = 0; i < H::kTiles; ++i)
+    for (int i0 = 0; i0 < H::kTiles; i0 += kSumTiles) {
+      __syncthreads();   // every wave is done with the stage, or with the last tiles' sums
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        sums[(wave * H::kTiles + i) * 256 + 4 * lane + v] =
-            WIDE ? (Sum)acc.d[WIDE ? i : 0][v] : (Sum)acc.f[i][v];
-    __syncthreads();
+      for (int i = i0; i < i0 + kSumTiles && i < H::kTiles; ++i)
 #pragma unroll
-    for (int i = 0; i < H::kTiles; ++i) {
-      double s = 0.0;
+        for (int v = 0; v < 4; ++v)
+          sums[(wave * kSumTiles + i - i0) * 256 + 4 * lane + v] = acc.d[i][v];
+      __syncthreads();
 #pragma unroll
-      for (int w = 0; w < kGramWaves; ++w) s += (double)sums[(w * H::kTiles + i) * 256 + tid];
-      tot[i] = (float)s;
+      for (int i = i0; i < i0 + kSumTiles && i < H::kTiles; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kGramWaves; ++w) s += sums[(w * kSumTiles + i - i0) * 256 + tid];
+        tot[i] = s;
+      }
     }
     if (!rescale || pass == 1) break;
     // This thread's entry of every tile is (er, ec); the diagonal judges the
@@ -274,8 +275,8 @@ __device__ __forceinline__ void gram_slice(const uint16_t* __restrict__ rows, in
     const int er = 4 * (tid >> 6) + (tid & 3), ec = (tid >> 2) & 15;
 #pragma unroll
     for (int a = 0; a < KS; ++a) {
-      const float d = tot[gram_tile(KS, a, a)];
-      const bool o = !(d >= 0x1p-80f && d <= 0x1p120f) && 16 * a + er < g;
+      const double d = tot[gram_tile(KS, a, a)];
+      const bool o = !(d >= 0x1p-80 && d <= 0x1p120) && 16 * a + er < g;
       if (er == ec) {
         ex[16 * a + er] = o ? 1 : 0;
         odd = odd || o;
@@ -300,7 +301,8 @@ __device__ __forceinline__ void gram_slice(const uint16_t* __restrict__ rows, in
 #pragma unroll
   for (int a = 0; a < KS; ++a)
 #pragma unroll
-    for (int c = a; c < KS; ++c) part[gram_tile(KM, a, c) * 256 + tid] = tot[gram_tile(KS, a, c)];
+    for (int c = a; c < KS; ++c)
+      part[gram_tile(KM, a, c) * 256 + tid] = (Part)tot[gram_tile(KS, a, c)];
   if (rescale) {
     if (tid == 0) gex[16 * KM] = again ? 1 : 0;
     if (again && tid < H::KP) gex[tid] = ex[tid];
@@ -316,24 +318,22 @@ constexpr int gram_lds_elems(int km) {
 }
 
 // gram_slice in the shape of the prompt's group size.
-// WIDE: as in GramAcc, for groups above 32 too (80 more registers; groups up
-// to 32 always).
-template <int KM, bool WIDE, class Between>
+template <int KM, class Part, class Between>
 __device__ __forceinline__ void gram_slice_of(const uint16_t* __restrict__ rows, int64_t ld, int g,
                                               int64_t c_lo, int64_t c_hi, uint16_t* stage,
-                                              int32_t* ex, bool rescale, float* __restrict__ part,
+                                              int32_t* ex, bool rescale, Part* __restrict__ part,
                                               int32_t* __restrict__ gex, int32_t* d_status,
                                               Between&& between) {
   if (KM == 1 || g <= 16)
-    gram_slice<KM, 1, true>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex, d_status, between);
+    gram_slice<KM, 1>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex, d_status, between);
   else if (KM == 2 || g <= 32)
-    gram_slice<KM, (KM < 2 ? KM : 2), true>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
+    gram_slice<KM, (KM < 2 ? KM : 2)>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
                                       d_status, between);
   else if (KM == 3 || g <= 48)
-    gram_slice<KM, (KM < 3 ? KM : 3), WIDE>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
+    gram_slice<KM, (KM < 3 ? KM : 3)>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
                                       d_status, between);
   else
-    gram_slice<KM, (KM < 4 ? KM : 4), WIDE>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
+    gram_slice<KM, (KM < 4 ? KM : 4)>(rows, ld, g, c_lo, c_hi, stage, ex, rescale, part, gex,
                                       d_status, between);
 }
 

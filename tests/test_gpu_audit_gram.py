@@ -106,6 +106,56 @@ def test_replicates_past_the_slices_are_drawn(R):
         assert torch.equal(torch.cat([x[key] for x in parts], dim=1), one[key])
 
 
+@pytest.mark.parametrize("sizes,D", [([64, 33], 1 << 20), ([48, 50], (1 << 21) + 2056)])
+def test_long_rows_are_summed_in_short_runs(sizes, D):
+    """Rows far longer than 128 slices of 2048 columns, with a component ten
+    times the rest in common: K's fp32 runs are 128 columns each, so their
+    roundings are N = D / 128 independent ones of 2^-24 at most, and e_r and
+    |t|^2 are within 2^-24 / sqrt(N) of A^2, what cancels in them (runs over a
+    whole slice round with a bias instead: 1.1 to 2.8 times this bound, now 0.07 to
+    0.21 of it).  The fold's centring adds 2^-23 A_r |delta_r S| / sqrt(G)."""
+    rng = np.random.default_rng(D)
+    off = np.zeros(len(sizes) + 1, dtype=np.int64)
+    off[1:] = np.cumsum(sizes)
+    nv, B, R, gmax = int(off[-1]), len(sizes), 20, max(sizes)
+    rewards = rng.random(nv).astype(np.float32)
+    p = rng.uniform(0.2, 1.0, nv).astype(np.float32)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(D)
+    common = 10.0 * torch.randn(D, generator=gen, device=DEV)
+    s = torch.empty((nv, D), dtype=torch.bfloat16, device=DEV)
+    for i in range(nv):
+        s[i] = (torch.randn(D, generator=gen, device=DEV) + common).to(torch.bfloat16)
+    dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
+    log(f"audit gram long rows sizes={sizes} D={D}")
+    got = pair.audit(dev[0], s, dev[1], dev[2], 9, 3, R, gmax, nv=nv)
+    way = pair.audit_direction(dev[0], s, dev[1], dev[2], 9, 3, R, gmax, nv=nv)
+    torch.cuda.synchronize()
+    assert int(got["status"].item()) == 0 and int(way["status"].item()) == 0
+    d = oracle.design_inclusion(off, p, 9, 3, R, gmax)
+    full, _ = oracle.pair_coeffs(off, rewards)
+    u = np.stack([oracle.pair_coeffs(off, rewards, d["mask"][r], d["pi"])[0] for r in range(R)])
+    rows = torch.from_numpy(np.concatenate([u - full, full[None]])).to(DEV)
+    eps = 2.0 ** -24 / np.sqrt(D / 128)
+    for b in range(B):
+        lo, hi = int(off[b]), int(off[b + 1])
+        sq = torch.zeros(R + 1, dtype=torch.float64, device=DEV)
+        norm = torch.zeros(hi - lo, dtype=torch.float64, device=DEV)
+        for c in range(0, D, 1 << 16):
+            x = s[lo:hi, c:c + (1 << 16)].double()
+            sq += (rows[:, lo:hi] @ x).square().sum(1)
+            norm += x.square().sum(1)
+        sq, norm = sq.cpu().numpy(), norm.sqrt().cpu().numpy()
+        A = ((np.abs(u) + np.abs(full))[:, lo:hi] * norm).sum(1)
+        e = got["rep_sqerr"][b].double().cpu().numpy()
+        worst = np.max(np.abs(e - sq[:R]) / (eps * A ** 2 + 2.0 ** -23 * A * np.sqrt(sq[:R] / (hi - lo))))
+        At = (np.abs(full[lo:hi]) * norm).sum()
+        t2 = float(way["target_norm"][b]) ** 2
+        tn = abs(t2 - sq[R]) / (eps * At ** 2 + 2.0 ** -23 * At * np.sqrt(sq[R] / (hi - lo)))
+        log(f"  in units of the bound: e {worst:.3f}, target {tn:.3f}")
+        assert worst <= 1.0 and tn <= 1.0
+
+
 def test_nonfinite_score_raises_in_any_slice():
     off, rewards, p, s, gmax = _case([16, 33], 5000, "normal", 4)
     dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
