@@ -372,12 +372,15 @@ size_t pair_audit_workspace_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R)
  *     mse  = (1/R) sum_r e_r
  *     bias = || (1/R) sum_r g_r - t ||
  * The R x D estimates are never materialised: with delta_r = A~^(r) - a and
- * K = S_b S_b^T, e_r = delta_r K delta_r^T, and the bias is the same form of
- * the mean row.  K is formed on the matrix cores from exact products with fp32
- * sums of short runs, moved to fp64; the fold is fp32, the quadratic
- * forms fp64.  So |Delta e_r| is a small multiple of 2^-24 A_r^2 with
- * A_r = sum_i (|A~^(r)_i| + |a_i|) |s_i|: about 1e-7 of e_r unless the rows
- * nearly cancel in delta_r S_b.  A replicate's e_r does not depend
+ * K = S_b S_b^T, e_r = delta_r K delta_r^T.  K is formed on the matrix cores
+ * from exact products with fp32 sums of 128 columns, moved to fp64; the fold
+ * is fp32, the quadratic forms fp64.  So |Delta e_r| is a small multiple of
+ * 2^-24 A_r^2 with A_r = sum_i (|A~^(r)_i| + |a_i|) |s_i|: about 1e-7 of e_r
+ * unless the rows nearly cancel in delta_r S_b.  The bias is the same form of
+ * the mean row, summed in fp64, unless it cancels in K; then the prompt's rows
+ * are read again and (1/R) sum_r delta_r S_b is summed per column in fp64.  So
+ * |Delta bias| is at most a small multiple of 2^-24 times the mean of A_r,
+ * also where a component common to all rows cancels.  A replicate's e_r does not depend
  * on R or rep0: calls over
  * consecutive replicate ranges return bitwise the rep_sqerr of one call over
  * their union.  Weights use rho = pi_w when given (e.g. all ones replays the

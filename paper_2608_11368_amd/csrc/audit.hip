@@ -34,7 +34,8 @@
 //  3. audit_eval    64 replicates per wave: the fold of their indicators over
 //                   the edge table (fp32 matrix instructions) and the
 //                   quadratic form (fp64 matrix instructions).
-//  4. audit_final   one wave per prompt: MSE, bias, or the mean cosine.
+//  4. audit_final   MSE, bias, or the mean cosine; prompts whose bias nearly
+//                   cancels in K are taken from the score rows.
 #include "common.hpp"
 #include "gram.hpp"
 #include "launch.hpp"
@@ -45,7 +46,10 @@ namespace {
 
 constexpr int kEvalThreads = 256;
 constexpr int kTableThreads = 256;
+constexpr int kFinalThreads = 256;
+constexpr int64_t kFinalCols = 8 * kFinalThreads;   // columns of an audit_final step
 constexpr int64_t kMaxSlices = 128;   // score-column slices per prompt at most
+constexpr int64_t kMaxBiasSlices = 32;
 constexpr int64_t kDrawRun = 512;     // replicates a stream workgroup draws at most, about
 
 // Groups that may exceed 48: the fp64 sums of ten tiles leave no registers for
@@ -63,8 +67,10 @@ struct AuditLayout {
   int64_t slots;   // audit_stream workgroups per prompt: nsl slices, and those that only draw
   int64_t nchunk;  // audit_eval workgroups per prompt
   int rounds;      // and times 64 replicates each of their waves takes
+  int64_t nbias;   // audit_final workgroups per prompt (column slices of the bias row)
+  int64_t bslice;  // and columns of each
   size_t part_off, gex_off, k_off, w_off, v_off, a_off, flag_off, bits_off, epart_off, dpart_off,
-      need;
+      bpart_off, count_off, need;
 };
 
 // The slicing depends on gmax and D alone, so that a prompt's K, and with it
@@ -90,6 +96,9 @@ AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   // R and gmax alone: the sums' order is the prompt's own.
   L.rounds = R >= 2048 && L.ks <= 2 ? 2 : 1;
   L.nchunk = ceil_div(R, (int64_t)L.rounds * kEvalThreads);
+  const int64_t nbias = L.nsl < kMaxBiasSlices ? L.nsl : kMaxBiasSlices;
+  L.bslice = round_up(ceil_div(D, nbias), kFinalCols);
+  L.nbias = ceil_div(D, L.bslice);
   size_t off = 0;
   auto take = [&](int64_t bytes) {
     const size_t at = off;
@@ -105,7 +114,9 @@ AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   L.flag_off = take(B * 4);                                    // 1: some rewards differ
   L.bits_off = take(B * R * 8);                                // indicators
   L.epart_off = take(B * L.nchunk * 8);                        // sums of e_r (of cos_r)
-  L.dpart_off = take(B * L.nchunk * L.kp * 4);                 // sums of the centred folds
+  L.dpart_off = take(B * L.nchunk * L.kp * 8);                 // sums of the deviations
+  L.bpart_off = take(B * L.nbias * 8);                         // squared bias of the column slices
+  L.count_off = take(B * 4);                                   // and how many are there
   L.need = off;
   return L;
 }
@@ -248,7 +259,7 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
     int32_t rule, float wmax, int64_t nsl, int skip_equal, const double* __restrict__ part,
     const int32_t* __restrict__ gex, double* __restrict__ K, float* __restrict__ wt,
     float* __restrict__ vt, double* __restrict__ a_out, int32_t* __restrict__ flag,
-    int32_t* d_status) {
+    int32_t* __restrict__ count, int32_t* d_status) {
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
   __shared__ float pl[KP], rl[KP];
@@ -319,7 +330,10 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
       a_out[b * KP + lane] = (double)a_full;
     }
     const bool differ = __ballot(vert && !(r_i == lane_value(r_i, 0))) != 0ull;
-    if (lane == 0) flag[b] = differ ? 1 : 0;
+    if (lane == 0) {
+      flag[b] = differ ? 1 : 0;
+      count[b] = 0;
+    }
   }
   __syncthreads();
   bool bad_rho = false;
@@ -438,14 +452,14 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     int64_t nchunk, int rounds, const double* __restrict__ K, const float* __restrict__ wt,
     const float* __restrict__ vt, const double* __restrict__ a_full,
     const int32_t* __restrict__ flag, const uint64_t* __restrict__ bits,
-    double* __restrict__ epart, float* __restrict__ dpart, float* __restrict__ rep_sqerr,
+    double* __restrict__ epart, double* __restrict__ dpart, float* __restrict__ rep_sqerr,
     int32_t* __restrict__ edge_count, double* __restrict__ target_norm) {
   constexpr int KP = 16 * KS;
   constexpr int NC = KS <= 2 ? 4 : 2;   // blocks of 16 replicates at once
   constexpr int kWaves = kEvalThreads / kWave;
   __shared__ __align__(16) double Ks[KP * KP];
   __shared__ __align__(16) float Ws[KP * KP];
-  __shared__ float wsum[kWaves][KP];
+  __shared__ double wsum[kWaves][KP];
   __shared__ double red[kWaves];
   __shared__ double recip[PAIR_GMAX_LIMIT + 1];
   __shared__ float recip32[PAIR_GMAX_LIMIT + 1];
@@ -574,15 +588,14 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     if (chunk == 0 && tid == 0) target_norm[b] = tt > 0.0 ? sqrt(tt) : 0.0;
   }
 
-  // Sums of the centred folds, times the normaliser where it varies.
-  // (Factors instead of branches: the blocks of replicates stay one basic block,
-  // whose chains interleave.)
-  const float varies = (rule == PAIR_RULE_RATIO_KE || rule == PAIR_RULE_SELFNORM) ? 1.0f : 0.0f;
-  float csum[KS][4];
+  // Sums of the deviations, in fp64: what cancels in them is sqrt(R) times
+  // the mean.  (A factor instead of a branch: the blocks of replicates stay one
+  // basic block, whose chains interleave.)
+  double dsum[KS][4];
 #pragma unroll
   for (int ib = 0; ib < KS; ++ib)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) csum[ib][v] = 0.0f;
+    for (int v = 0; v < 4; ++v) dsum[ib][v] = 0.0;
   double esum = 0.0;
   const int steps = rounds * (4 / NC);
 #pragma unroll 1
@@ -639,7 +652,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
           sum += C[ib][cb][v];
         }
       const float mean = group_sum(sum) * recip32[k[cb]];
-      const float weight = __builtin_fmaf(varies, (float)inv[cb], 1.0f - varies);
+      const double counts = r0 + 16 * cb < R ? 1.0 : 0.0;   // replicates past R do not
 #pragma unroll
       for (int ib = 0; ib < KS; ++ib)
 #pragma unroll
@@ -649,7 +662,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
             x[ib][cb][v] = (double)c * inv[cb];
           } else {
             x[ib][cb][v] = __builtin_fma((double)c, inv[cb], -af[ib][v]);
-            csum[ib][v] = __builtin_fmaf(c, weight, csum[ib][v]);
+            dsum[ib][v] = __builtin_fma(counts, x[ib][cb][v], dsum[ib][v]);
           }
         }
     }
@@ -699,7 +712,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     for (int ib = 0; ib < KS; ++ib)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float s = row_sum(csum[ib][v]);
+        const double s = row_sum_d(dsum[ib][v]);
         if ((lane & 15) == 0) wsum[wave][16 * ib + 4 * grp + v] = s;
       }
   }
@@ -711,7 +724,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     epart[b * nchunk + chunk] = t;
   }
   if (!COS && tid < KP) {
-    float s = 0.0f;
+    double s = 0.0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) s += wsum[w][tid];
     dpart[(b * nchunk + chunk) * KP + tid] = s;
@@ -719,58 +732,145 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// 4. Fixed-order reductions over the replicate chunks, one wave per prompt.
+// 4. Fixed-order reductions over the replicate chunks: the MSE (or the mean
+//    cosine) and the bias norm |delta_bar S|.
+//
+//    The quadratic form delta_bar K delta_bar^T carries K's rounding (4e-9 of what
+//    cancels in it) into the bias norm, so its relative error grows with the square of the
+//    cancellation, where a sum per score column grows with its first power.  K
+//    serves while the form is at least 1 / kCancel of sum_i delta_bar_i^2 K_ii (1e-7 at
+//    the most); below that, as with a component that all rows of a prompt
+//    share, the prompt's rows are read again and delta_bar S is summed column by
+//    column in fp64.  Every workgroup of a prompt decides for itself (the
+//    form takes it as long as asking another), and the last of them adds the slices in order.
+//    G = 16, D = 4096, R = 1000, a common component of 100 times the rest: the form alone
+//    is off by 1e-4 of the norm, so 1e-6.  B = 256, G = 16, D = 65536, R = 4096: 4.6 us
+//    with the form alone and a wave per prompt, 6.6 us so, and 190 us where every prompt is read again.
 // ---------------------------------------------------------------------------
+constexpr double kCancel = 64.0;
+
 template <bool COS>
-__global__ __launch_bounds__(kWave) void audit_final_kernel(
-    int64_t nv, int32_t gmax, int kp, const int64_t* __restrict__ offsets, int32_t rule, int64_t R,
-    int64_t nchunk, const double* __restrict__ K, const double* __restrict__ a_full,
-    const int32_t* __restrict__ flag,
-    const double* __restrict__ epart, const float* __restrict__ dpart, double* __restrict__ first,
-    double* __restrict__ bias_norm) {
-  const int64_t b = blockIdx.x;
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(kFinalThreads) void audit_final_kernel(
+    int64_t nv, int32_t gmax, int kp, const int64_t* __restrict__ offsets, int64_t D,
+    const uint16_t* __restrict__ scores, int64_t ld, int nbias, int64_t bslice, int64_t R,
+    int64_t nchunk, const double* __restrict__ K, const int32_t* __restrict__ flag,
+    const double* __restrict__ epart, const double* __restrict__ dpart, double* bpart,
+    int32_t* count, double* __restrict__ first, double* __restrict__ bias_norm) {
+  __shared__ double dl[kWave];
+  __shared__ double form, sh[kFinalThreads / kWave];
+  __shared__ int by_column;
+  const int slot = (int)(blockIdx.x % (uint32_t)nbias);
+  const int64_t b = blockIdx.x / (uint32_t)nbias;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   int64_t o0, g64;
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
   const int g = (int)g64;
   if (!COS && flag[b] == 0) {   // equal rewards: exact zeros
-    if (lane == 0) {
+    if (slot == 0 && tid == 0) {
       first[b] = 0.0;
       bias_norm[b] = 0.0;
     }
     return;
   }
-  double t = 0.0;
-  for (int64_t c = lane; c < nchunk; c += kWave) t += epart[b * nchunk + c];
-  t = wave_sum_d(t);
-  if (lane == 0) first[b] = t / (double)R;   // the MSE, or the mean cosine
+  if (wave == (COS ? 0 : 1) && slot == 0) {
+    double t = 0.0;
+    for (int64_t c = lane; c < nchunk; c += kWave) t += epart[b * nchunk + c];
+    t = wave_sum_d(t);
+    if (lane == 0) first[b] = t / (double)R;   // the MSE, or the mean cosine
+  }
   if (COS) return;
-  double d = 0.0;
-  if (lane < g) {
-    int64_t c = 0;
-    for (; c + 8 <= nchunk; c += 8) {   // eight loads in flight
-      float v[8];
+  if (wave == 0) {
+    double d = 0.0;
+    if (lane < g) {
+      int64_t c = 0;
+      for (; c + 8 <= nchunk; c += 8) {   // eight loads in flight
+        double v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = dpart[(b * nchunk + c + q) * kp + lane];
+        for (int q = 0; q < 8; ++q) v[q] = dpart[(b * nchunk + c + q) * kp + lane];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) d += (double)v[q];
+        for (int q = 0; q < 8; ++q) d += v[q];
+      }
+      for (; c < nchunk; ++c) d += dpart[(b * nchunk + c) * kp + lane];
+      d = d / (double)R;
     }
-    for (; c < nchunk; ++c) d += (double)dpart[(b * nchunk + c) * kp + lane];
-    // mean of u, less the target's coefficients
-    const bool uniform = rule != PAIR_RULE_RATIO_KE && rule != PAIR_RULE_SELFNORM;
-    d = d / ((double)R * (uniform ? (double)(g * (g - 1)) : 1.0)) - a_full[b * kp + lane];
-  }
-  double y = 0.0;
-  for (int j0 = 0; j0 < g; j0 += 16) {
-    double v[16];
+    const double* Kb = K + b * (kp * kp);
+    const int row = lane < g ? lane : 0;   // lanes past the group read row 0
+    const double kii = Kb[frag_place64(kp, row, row)];
+    double y = 0.0;
+    for (int j0 = 0; j0 < g; j0 += 16) {
+      double v[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q)   // lanes past the group read row 0
-      v[q] = K[b * (kp * kp) + frag_place64(kp, lane < g ? lane : 0, j0 + q)];
+      for (int q = 0; q < 16; ++q) v[q] = Kb[frag_place64(kp, row, j0 + q)];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) y = __builtin_fma(v[q], readlane_d(d, j0 + q), y);
+      for (int q = 0; q < 16; ++q) y = __builtin_fma(v[q], readlane_d(d, j0 + q), y);
+    }
+    const double q = wave_sum_d(d * y);   // d is 0 past the group
+    const double own = wave_sum_d(d * d * kii);
+    dl[lane] = d;
+    if (lane == 0) {
+      form = q;
+      by_column = !(q * kCancel >= own) ? 1 : 0;
+    }
   }
-  const double q = wave_sum_d(d * y);   // d is 0 past the group
-  if (lane == 0) bias_norm[b] = q > 0.0 ? sqrt(q) : (q == q ? 0.0 : q);
+  __syncthreads();
+  if (by_column == 0) {
+    if (slot == 0 && tid == 0) bias_norm[b] = sqrt(form);
+    return;
+  }
+
+  // Eight columns per thread and step, eight rows in flight.  Rows past the
+  // group repeat the last one, with the factor 0.
+  const uint16_t* rows = scores + o0 * ld;
+  const int64_t c_lo = slot * bslice, c_hi = c_lo + bslice < D ? c_lo + bslice : D;
+  double sq = 0.0;
+  for (int64_t c = c_lo + 8 * tid; c < c_hi; c += kFinalCols) {
+    double y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = 0.0;
+    if (c + 8 <= c_hi) {
+      for (int i0 = 0; i0 < g; i0 += 8) {
+        uint4 v[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const int i = i0 + s < g ? i0 + s : g - 1;
+          v[s] = load_nt16(rows + (int64_t)i * ld + c);
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const double f = dl[i0 + s];
+          const uint32_t w[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            y[2 * e] = __builtin_fma(f, (double)bf16lo_to_f32(w[e]), y[2 * e]);
+            y[2 * e + 1] = __builtin_fma(f, (double)bf16hi_to_f32(w[e]), y[2 * e + 1]);
+          }
+        }
+      }
+    } else {   // the row's last columns
+      for (int i = 0; i < g; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (c + e < c_hi)
+            y[e] = __builtin_fma(dl[i], (double)bf16lo_to_f32(rows[(int64_t)i * ld + c + e]), y[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sq = __builtin_fma(y[e], y[e], sq);
+  }
+  sq = wave_sum_d(sq);
+  if (lane == 0) sh[wave] = sq;
+  __syncthreads();
+  if (tid != 0) return;
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < kFinalThreads / kWave; ++w) t += sh[w];
+  // The slices' sums cross workgroups: stored and read past the caches of one XCD.
+  __hip_atomic_store(bpart + b * nbias + slot, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__hip_atomic_fetch_add(count + b, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != nbias - 1)
+    return;
+  t = 0.0;
+  for (int s = 0; s < nbias; ++s)
+    t += __hip_atomic_load(bpart + b * nbias + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  bias_norm[b] = sqrt(t);
 }
 
 struct AuditArgs {
@@ -805,13 +905,17 @@ int run_audit(const AuditLayout& L, const AuditArgs& A) {
   int32_t* flag = reinterpret_cast<int32_t*>(ws + L.flag_off);
   uint64_t* bits = reinterpret_cast<uint64_t*>(ws + L.bits_off);
   double* epart = reinterpret_cast<double*>(ws + L.epart_off);
-  float* dpart = reinterpret_cast<float*>(ws + L.dpart_off);
+  double* dpart = reinterpret_cast<double*>(ws + L.dpart_off);
+  double* bpart = reinterpret_cast<double*>(ws + L.bpart_off);
+  int32_t* count = reinterpret_cast<int32_t*>(ws + L.count_off);
   const uint16_t* s = static_cast<const uint16_t*>(A.scores);
 
   // Every grid size is checked before the first launch.
   const int64_t stream_grid = A.B * L.slots, eval_grid = A.B * L.nchunk;
   const int64_t table_grid = A.B * (gram_tiles(KS) + 1);
-  if (stream_grid > 0x7fffffffLL || eval_grid > 0x7fffffffLL || table_grid > 0x7fffffffLL)
+  const int64_t nbias = COS ? 1 : L.nbias, final_grid = A.B * nbias;
+  if (stream_grid > 0x7fffffffLL || eval_grid > 0x7fffffffLL || table_grid > 0x7fffffffLL ||
+      final_grid > 0x7fffffffLL)
     return PAIR_ERANGE;
   // The cosine audit reports what its Gram matrix holds, so it reads every
   // prompt and leaves the products unscaled: an overflow is a non-finite entry.
@@ -824,16 +928,16 @@ int run_audit(const AuditLayout& L, const AuditArgs& A) {
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
   hipLaunchKernelGGL((audit_tables_kernel<KS>), dim3((unsigned)table_grid), dim3(kTableThreads), 0,
                      A.stream, A.nv, A.gmax, A.offsets, A.rewards, A.p, A.pi_w, A.rule, A.wmax,
-                     L.nsl, own, part, gex, K, wt, vt, a, flag, A.d_status);
+                     L.nsl, own, part, gex, K, wt, vt, a, flag, count, A.d_status);
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
   hipLaunchKernelGGL((audit_eval_kernel<KS, COS>), dim3((unsigned)eval_grid), dim3(kEvalThreads), 0,
                      A.stream, A.nv, A.gmax, A.offsets, A.rule, A.R, L.nchunk, L.rounds, K, wt, vt,
                      a, flag, bits, epart, dpart, A.rep_sqerr, A.edge_count,
                      COS ? A.second : nullptr);
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-  hipLaunchKernelGGL((audit_final_kernel<COS>), dim3((unsigned)A.B), dim3(kWave), 0, A.stream, A.nv,
-                     A.gmax, L.kp, A.offsets, A.rule, A.R, L.nchunk, K, a, flag, epart, dpart, A.first,
-                     A.second);
+  hipLaunchKernelGGL((audit_final_kernel<COS>), dim3((unsigned)final_grid), dim3(kFinalThreads), 0,
+                     A.stream, A.nv, A.gmax, L.kp, A.offsets, A.D, s, A.ld, (int)nbias, L.bslice,
+                     A.R, L.nchunk, K, flag, epart, dpart, bpart, count, A.first, A.second);
   return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
 }
 

@@ -156,6 +156,56 @@ def test_long_rows_are_summed_in_short_runs(sizes, D):
         assert worst <= 1.0 and tn <= 1.0
 
 
+@pytest.mark.parametrize("rule,R,c,D", [
+    (pair.RULE_UNWEIGHTED, 200, 100.0, 4096), (pair.RULE_UNWEIGHTED, 200, 300.0, 70001),
+    (pair.RULE_HT, 8, 300.0, 4096), (pair.RULE_HT, 8, 300.0, 70001)])
+def test_bias_norm_with_a_common_component(rule, R, c, D):
+    """Score rows that share a component c times the rest, except in the last
+    prompt: |delta_bar S| cancels by about c sqrt(G).  Its error grows with the first
+    power of that, as a sum per score column does: the coefficients carry
+    a few roundings of 2^-24, so |Delta bias| <= 2^-23 A with A the mean over
+    replicates of A_r (for the unweighted rule and rewards in {0, 1} the folds
+    are whole numbers, and A is that of the target alone).  The quadratic form
+    of K by itself misses this by up to 20."""
+    rng = np.random.default_rng(int(c) + D)
+    sizes = [16, 5, 64, 33, 20]
+    off = np.zeros(len(sizes) + 1, dtype=np.int64)
+    off[1:] = np.cumsum(sizes)
+    nv, gmax = int(off[-1]), 64
+    whole = rule == pair.RULE_UNWEIGHTED
+    rewards = (rng.permutation(nv) % 2 if whole else rng.random(nv)).astype(np.float32)
+    p = rng.uniform(0.2, 1.0, nv).astype(np.float32)
+    ld = (D + 7) // 8 * 8
+    x = np.full((nv, ld), np.nan, dtype=np.float32)
+    x[:, :D] = rng.standard_normal((nv, D))
+    x[:off[-2], :D] += np.float32(c) * rng.standard_normal(D).astype(np.float32)
+    s = torch.from_numpy(x).to(torch.bfloat16)
+    dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
+    sd = s.to(DEV)[:, :D]
+    log(f"audit bias, common component {c} D={D} R={R} rule={rule}")
+    ws = torch.full((pair.pair_audit_workspace_bytes(len(sizes), gmax, D, R),), 255,
+                    dtype=torch.uint8, device=DEV)
+    got = [pair.audit(dev[0], sd, dev[1], dev[2], 3, 0, R, gmax, nv=nv, rule=rule, workspace=ws)
+           for _ in range(2)]
+    torch.cuda.synchronize()
+    assert int(got[0]["status"].item()) == 0
+    assert torch.equal(got[0]["bias_norm"], got[1]["bias_norm"])
+    d = oracle.design_inclusion(off, p, 3, 0, R, gmax)
+    full, _ = oracle.pair_coeffs(off, rewards)
+    u = np.stack([oracle.pair_coeffs_rule(off, rewards, d["mask"][r], d["pi"], rule)["coeff"]
+                  for r in range(R)])
+    S = s[:, :D].double().numpy()
+    norm = np.sqrt((S ** 2).sum(1))
+    A = norm * (np.abs(full) + (0.0 if whole else np.abs(u).mean(0)))
+    for b in range(len(sizes)):
+        lo, hi = int(off[b]), int(off[b + 1])
+        want = np.linalg.norm((u - full).mean(0)[lo:hi] @ S[lo:hi])
+        unit = 2.0 ** -23 * A[lo:hi].sum()
+        err = abs(float(got[0]["bias_norm"][b]) - want) / unit
+        log(f"  G={hi - lo}: {err:.3f} of the bound, which is {unit / want:.1e} of the norm")
+        assert err <= 1.0
+
+
 def test_nonfinite_score_raises_in_any_slice():
     off, rewards, p, s, gmax = _case([16, 33], 5000, "normal", 4)
     dev = [torch.from_numpy(a).to(DEV) for a in (off, rewards, p)]
