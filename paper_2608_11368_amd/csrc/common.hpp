@@ -10,6 +10,15 @@ namespace pair {
 
 constexpr int kWave = 64;
 
+// Between a wave's LDS accesses where lanes read or overwrite what other lanes
+// of the same wave wrote or read.  The hardware keeps a wave's LDS accesses in
+// order and needs no wait; this keeps the compiler from moving them past one
+// another, which it may where each lane's own addresses differ.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 counter-based generator (Salmon, Moraes, Dror, Shaw, SC'11).
 // Ten rounds; each round forms the full 128-bit products of counter words 0

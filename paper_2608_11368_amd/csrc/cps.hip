@@ -135,7 +135,7 @@ __device__ __forceinline__ void eliminate(int k0, int lane, double (&a)[KP], dou
   for (int s = 0; s < kPivots; ++s) {
     double* v = buf + (s & 1) * (2 * kWave);   // upper half zero: columns past the wave
     v[lane] = a[s];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     const double* vk = v + k0;
     const int c0 = (s + 1) & ~1;   // pairs of entries, 16 bytes a load
     const int n = (W - c0 + kChunk - 1) / kChunk;

@@ -114,6 +114,7 @@ __device__ __forceinline__ void gram_pass(const uint16_t* __restrict__ rows, int
         *put_at(t) = x;
       }
     }
+    wave_lds_order();   // the rows are staged
     // Fragment of row block q, step s: row 16 q + l % 16, columns 32 s +
     // 8 (l / 16) .. + 7 (the order of the 32 products does not matter as
     // long as both operands share it).
@@ -140,6 +141,7 @@ __device__ __forceinline__ void gram_pass(const uint16_t* __restrict__ rows, int
         }
       }
     }
+    wave_lds_order();   // and read
   };
 
   uint4 v[H::kLoads];
