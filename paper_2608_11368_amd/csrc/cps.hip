@@ -42,7 +42,6 @@ namespace pair {
 
 namespace {
 
-constexpr int kManyClose = 32;     // see the joint block
 constexpr int kMaxFitIter = 200;   // evaluations of pi(w), rejected steps included
 
 // e_0..e_{KP-1} (only k <= n meaningful) of the units 0..g-1 excluding skip1
@@ -61,6 +60,13 @@ __device__ __forceinline__ void esp_excl(double w, int g, int n, int skip1, int 
       if (k <= n) e[k] = __dadd_rn(e[k], __dmul_rn(wm, e[k - 1]));
   }
 }
+
+// Close pairs of a row of the joint block from which every lane's own polynomial
+// is the faster: it costs all lanes g * KP steps whatever the number, a pair by
+// the wave g steps of another kind.  Equal at 4.7, 6.7, 9.6 and 14.7 pairs for
+// KP = 16, 32, 48, 64 (4.4, 13, 24 and 59 us a row against 0.9, 2.0, 2.5 and
+// 4.0 a pair at G = KP, 512 prompts).
+constexpr int many_close(int kp) { return kp / 5 + 1; }
 
 // e_k of the units but two, in lane k.
 __device__ __forceinline__ double esp_excl_wave(double w, int g, int lane, int skip1, int skip2) {
@@ -120,7 +126,9 @@ __device__ __forceinline__ double recip_d(double x) {
 // owns row i, shifted left by k0, of which W entries are left.  Every other
 // row is cleared of the pivot column, rows above included (Gauss-Jordan: the
 // lanes run anyway, and no back substitution is left).  The rows and columns
-// from the pivot on stay symmetric, so the pivot row is the pivot column: one
+// from the pivot on stay symmetric, so the pivot row is the pivot column (entries
+// of odds that agree to 1e-6 but form chains are symmetric to 1e-6 only, which
+// moves the Newton direction by as much and not what it converges to): one
 // store of it by all lanes, read back as broadcasts, kChunk entries in flight
 // while the last ones are used.  One wave, whose LDS accesses keep their order:
 // no waits but for the data.  Eight steps are unrolled, so that register indices
@@ -340,10 +348,11 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
     // (error below 1e-8, under the fp32 output's rounding); closer pairs
     // take the leave-two-out polynomial.
     // e_{n-2} of a few pairs is the wave's work, a lane per coefficient (the
-    // same operations in the same order, about 2,000 cycles a pair); from kManyClose
-    // pairs in a row on it is every lane's own polynomial, 65,000 cycles.
-    // Always the latter, a batch waited for the one prompt with a close pair:
-    // 235 us for 512 prompts of 2..64, where the fits take 115; now 136.
+    // same operations in the same order); from many_close() pairs in a row on
+    // it is every lane's own polynomial.  Always the latter, a batch waited for
+    // the one prompt with a close pair: 235 us for 512 prompts of 2..64, where
+    // the fits take 115; now 136.  The former up to 32 pairs, 512 prompts with equal
+    // targets took 223 us at G = 16 and 2005 at 32, always the latter 71 and 428.
     float* col = pi_joint + b * (int64_t)gmax * gmax + lane;
     for (int j = 0; j < gmax; ++j) {
       const double wj = readlane_d(w, j < g ? j : 0), pj = readlane_d(pi, j < g ? j : 0);
@@ -355,7 +364,7 @@ __global__ __launch_bounds__(kWave) void cps_fit_kernel(
       pij = (unit && j == lane) ? pi : pij;
       const bool direct = pair_ij && !sep && n >= 2;
       uint64_t close = __ballot(direct);
-      if (__popcll(close) >= kManyClose) {
+      if (__popcll(close) >= many_close(KP)) {
         double e2[KP];
         esp_excl<KP>(w, g, n - 2, lane, j, e2);   // w of lane j is excluded too
         if (direct) pij = w * wj * pick<KP>(e2, n - 2) / en_last;

@@ -116,6 +116,50 @@ def test_fit_hard_targets_vs_oracle():
     assert its.max() <= 40
 
 
+@pytest.mark.parametrize("KP", [16, 32, 48, 64])
+def test_close_odds_vs_oracle(KP):
+    """Rows of the joint block with as many close pairs as the wave still takes
+    one by one, with one more, and with all (equal targets); and chains, in
+    which neighbours are close and the ends are not (steps of 4e-7: ties of the
+    Newton system to its neighbours only; steps of 4e-6: close in the joint block
+    alone), so that the tied entries differ from row to row.  G = KP and KP - 3."""
+    r = np.random.default_rng(KP)
+    edge = KP // 5 + 1
+    groups = []
+    for g in (KP, KP - 3):
+        n = g // 3
+        for m in (2, edge, edge + 1, g):
+            t = r.uniform(0.5, 1.5, g)
+            t[r.permutation(g)[:m]] = 1.0
+            groups.append(t * (n / t.sum()))
+        for step in (4e-7, 4e-6):
+            t = r.uniform(0.5, 1.5, g)
+            t[:g // 2] = 1.0 + step * np.arange(g // 2)
+            groups.append(t * (n / t.sum()))
+            t = 1.0 + step * np.arange(g)
+            groups.append(t * (n / t.sum()))
+    sizes = np.array([t.size for t in groups])
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    tgt = np.concatenate(groups).astype(np.float32)
+    log(f"cps fit close odds KP={KP}")
+    got = pair.cps_fit(_t(offsets), _t(tgt), KP, nv=int(offsets[-1]))
+    torch.cuda.synchronize()
+    assert int(got["status"].item()) == 0
+    w, its = got["w"].cpu().numpy(), got["iters"].cpu().numpy()
+    pj = got["pi_joint"].cpu().numpy()
+    worst_w, worst_p = 0.0, 0.0
+    for b, g in enumerate(sizes):
+        lo, hi = offsets[b], offsets[b + 1]
+        ow, it = oracle.cps_fit(tgt[lo:hi], g // 3)
+        assert it >= 0
+        worst_w = max(worst_w, float(np.max(np.abs(w[lo:hi] / ow - 1))))
+        _, opij = oracle.cps_inclusion(ow, g // 3)
+        worst_p = max(worst_p, float(np.max(np.abs(pj[b, :g, :g] - opij) / opij)))
+    log(f"  max w rel {worst_w:.2e}, max pi_ij rel {worst_p:.2e}, evaluations max {its.max()}")
+    assert worst_w <= 1e-9 and worst_p <= 1e-6
+    assert 0 <= its.min() and its.max() <= 8
+
+
 @pytest.mark.parametrize("R", [1, 300])
 def test_draw_bit_exact(R):
     w_ = wl.WORKLOADS["ragged"].replace(B=40)
