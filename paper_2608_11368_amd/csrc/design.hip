@@ -23,8 +23,10 @@
 // us for (B, G, R), wave against design_kernel: (128, 16, 1) 4.0 / 5.0,
 // (128, 16, 64) 7.2 / 5.5, (512, 2..8, 8) 5.2 / 5.6, (512, 2..8, 16) 6.6 / 5.6,
 // (512, 2..64, 1) 14.8 / 6.9, (512, 2..64, 1000) 231 / 48, (512, 64, 1024) 235 / 63.
-// So it takes launches of at most kWaveUnits waves and gmax <= 16 (a rho
-// block of at most four passes).
+// Without a rho block (512, 2..64, 1) 5.6 / 7.7, (512, 64, 8) 7.3 / 7.7,
+// (64, 30..40, 64) 7.3 / 7.8, (512, 2..64, 64) 22.7 / 12.0.
+// So it takes launches of at most kWaveUnits waves with gmax <= 16 (a rho
+// block of at most four passes) or without a rho block.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -243,7 +245,7 @@ int launch_design(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, c
                   int32_t* edge_count, int32_t* completed, int32_t* d_status, hipStream_t stream) {
   const bool draws = mask != nullptr || edge_count != nullptr || completed != nullptr;
   if (!draws && pi == nullptr) return PAIR_OK;
-  if (gmax <= 16 && B <= kWaveUnits && (!draws || R <= kWaveUnits / B)) {
+  if ((gmax <= 16 || pi == nullptr) && B <= kWaveUnits && (!draws || R <= kWaveUnits / B)) {
     const int64_t waves = draws ? B * R : B;   // the rho block needs replicate 0 only
     hipLaunchKernelGGL(design_wave_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream,
                        B, nv, gmax, offsets, p, seed, rep0, draws ? R : 1, mask, pi, edge_count,

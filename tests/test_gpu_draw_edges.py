@@ -43,6 +43,23 @@ def test_design_draws(name, R):
         assert np.array_equal(got[key].cpu().numpy(), want[key]), key
 
 
+@pytest.mark.parametrize("name,R", [("edges", 1), ("full", 256), ("full", 257), ("one", 4096),
+                                    ("one", 4097), ("twos", 125)])
+def test_design_draws_without_a_rho_block(name, R):
+    """Wide groups without a rho block, as many (replicate, prompt) pairs as a wave
+    each still takes (4096), and more."""
+    off = _offsets(name)
+    nv, gmax = int(off[-1]), max(SIZES[name])
+    p = np.random.default_rng(R).uniform(0.05, 1.0, nv).astype(np.float32)
+    log(f"design draws without rho {name} R={R}")
+    got = pair.design_inclusion(_t(off), _t(p), 12, 3, R, gmax, nv=nv, want_pi=False)
+    torch.cuda.synchronize()
+    want = oracle.design_inclusion(off, p, 12, 3, R, gmax)
+    assert int(got["status"].item()) == 0
+    for key in ("mask", "edge_count", "completed"):
+        assert np.array_equal(got[key].cpu().numpy(), want[key]), key
+
+
 @pytest.mark.parametrize("R", [1, 40])
 def test_design_optional_outputs_and_bad_prompts(R):
     """Each output alone is what it is beside the others; a malformed prompt and
