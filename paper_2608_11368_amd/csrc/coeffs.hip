@@ -17,6 +17,8 @@
 // are issued kStage and kFold at a time without a condition around them (a
 // guarded load waits for its turn): positions past the block repeat its last row or column.
 // B = 512, G in 2..64: 29-33 us with a guarded load and a 64-bit division per element, 19 us so.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -51,19 +53,28 @@ __global__ __launch_bounds__(64) void edge_coeffs_kernel(
     const int lg = 32 - __clz(n - 1);
     const int col = (lane & ((1 << lg) - 1)) < n ? (lane & ((1 << lg) - 1)) : n - 1;
     const int rows = kWave >> lg;
-    for (int i0 = lane >> lg; i0 < n; i0 += rows * kStage) {
-      float v[kStage];
+    auto stage = [&](auto loads) {
+      constexpr int N = decltype(loads)::value;
+      for (int i0 = lane >> lg; i0 < n; i0 += rows * N) {
+        float v[N];
 #pragma unroll
-      for (int s = 0; s < kStage; ++s) {
-        const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
-        v[s] = blk[i * gmax + col];
-      }
+        for (int s = 0; s < N; ++s) {
+          const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
+          v[s] = blk[i * gmax + col];
+        }
 #pragma unroll
-      for (int s = 0; s < kStage; ++s) {
-        const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
-        rho_lds[i * stride + col] = v[s];
+        for (int s = 0; s < N; ++s) {
+          const int i = i0 + s * rows < n ? i0 + s * rows : n - 1;
+          rho_lds[i * stride + col] = v[s];
+        }
       }
-    }
+    };
+    // Groups of up to 8 are one load a lane (kStage of them, all but one a repeat,
+    // cost 0.25 us of 7.7 at B = 2000, G in 2..8).
+    if (lg <= 3)
+      stage(std::integral_constant<int, 1>{});
+    else
+      stage(std::integral_constant<int, kStage>{});
   }
   __syncthreads();
 
