@@ -941,8 +941,21 @@ int run_audit(const AuditLayout& L, const AuditArgs& A) {
   return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
 }
 
+// Columns per slice of the column-by-column contraction.
+int64_t contraction_cols(int64_t ks) { return ks == 1 ? 2048 : (ks == 2 ? 1024 : 512); }
+
+// The range of a call is the one of that contraction, a workgroup per 256
+// replicates and (but for the cosine) per slice; the grids here are smaller.
+template <bool COS>
+bool out_of_range(const AuditArgs& A) {
+  const int64_t reps = ceil_div(COS ? A.R : A.R + 1, 256);
+  const int64_t slices = COS ? 1 : ceil_div(A.D, contraction_cols((A.gmax + 15) / 16));
+  return A.B * reps > 0x7fffffffLL || A.B * slices > 0x7fffffffLL;
+}
+
 template <bool COS>
 int launch_any(const AuditArgs& A) {
+  if (out_of_range<COS>(A)) return PAIR_ERANGE;
   const AuditLayout L = audit_layout(A.B, A.gmax, A.D, A.R);
   switch (L.ks) {
     case 1: return run_audit<1, COS>(L, A);
@@ -962,7 +975,7 @@ int launch_any(const AuditArgs& A) {
 static size_t contraction_bytes(int64_t B, int32_t gmax, int64_t D, int64_t R, bool direction) {
   const int64_t ks = (gmax + 15) / 16, kp = 16 * ks;
   const int64_t rrows = round_up(R, 64) + 32, nwg = ceil_div(R, 256);
-  const int64_t cols = ks == 1 ? 2048 : (ks == 2 ? 1024 : 512);
+  const int64_t cols = contraction_cols(ks);
   size_t n = (size_t)round_up(B * rrows * kp * 4, 256) + (size_t)round_up(B * nwg * gmax * 4, 256);
   if (direction)
     return n + (size_t)round_up((int64_t)exact_workspace_bytes(B, gmax, D), 256) +

@@ -495,11 +495,12 @@ int launch_cps_draw(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets,
                     const int32_t* n, uint64_t seed, int64_t rep0, int64_t R, uint8_t* mask,
                     int32_t* edge_count, int32_t* d_status, hipStream_t stream) {
   const int ks = (gmax + 15) / 16;
+  // The range of a call is that of a workgroup per 64 replicates.
+  if ((R + kWave - 1) / kWave > 0x7fffffffLL / B) return PAIR_ERANGE;
   // Replicates per workgroup: whole waves, no more of them than R needs.
   const int64_t reps = R < kDrawReps ? (R + kWave - 1) / kWave * kWave : kDrawReps;
   const int64_t nwg = (R + reps - 1) / reps;
   const int64_t grid = B * nwg;
-  if (grid > 0x7fffffffLL) return PAIR_ERANGE;
 #define PAIR_CPS_DRAW(KP_)                                                                     \
   hipLaunchKernelGGL(cps_draw_kernel<KP_>, dim3((unsigned)grid), dim3((unsigned)reps), 0, stream, B, nv, \
                      gmax, offsets, w, n, seed, rep0, R, nwg, mask, edge_count, d_status)

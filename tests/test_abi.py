@@ -141,6 +141,27 @@ def test_audit_noalloc_rejects_bad_arguments_and_oversized_prompts():
     assert "scratch" in pair.strerror(-7)
 
 
+def test_grids_beyond_the_range_are_refused():
+    """Sizes whose work, at 256 replicates or one slice of score columns to a
+    workgroup of an audit and 64 replicates to one of the fixed-size draw, exceeds
+    2^31 - 1 workgroups are outside the range of a call, however few the kernels
+    launch."""
+    L = pair.lib()
+
+    def audit(B, D, R, gmax=16):
+        ws = L.pair_audit_workspace_bytes(B, gmax, D, R)
+        return L.pair_audit(B, 2 * B, gmax, FAKE, D, FAKE, 1, D, FAKE, FAKE, NULL, 1, 0, R, FAKE,
+                            FAKE, NULL, NULL, FAKE, ws, NULL, NULL)
+
+    assert audit(0xC00000, 64, (1 << 16) - 1) == -3
+    assert audit(1 << 20, 1 << 33, 16) == -3
+    B, R = 0xC00000, (1 << 16) - 1
+    ws = L.pair_audit_direction_workspace_bytes(B, 16, 64, R)
+    assert L.pair_audit_direction(B, 2 * B, 16, FAKE, 64, FAKE, 1, 64, FAKE, FAKE, NULL, 0, 0.0, 1,
+                                  0, R, FAKE, FAKE, FAKE, ws, NULL, NULL) == -3
+    assert L.pair_cps_draw(0x7fffffff, 2, 8, FAKE, FAKE, FAKE, 1, 0, 65, FAKE, NULL, NULL, NULL) == -3
+
+
 def test_design_alloc_ex_rejects_bad_arguments():
     f = pair.lib().pair_design_alloc_ex
 
