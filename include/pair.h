@@ -414,11 +414,12 @@ int pair_audit(int64_t B, int64_t nv, int32_t gmax, const int64_t* offsets, int6
  * PAIR_AUDIT_SCRATCH_BYTES (64 MiB), which each GPU the library runs on holds
  * until the process ends (it is part of the library's device code, whether
  * or not this entry point is called).  The prompts are audited in
- * consecutive chunks whose pair_audit_workspace_bytes fits that array, so the
- * outputs are bitwise those of pair_audit with the same arguments (the audit
- * workload's shape, G = 16, D = 65536, R = 4096, takes about 80 prompts per
- * chunk).  If a single prompt needs more than the array it returns
- * PAIR_ESCRATCH and enqueues nothing.  The call allocates nothing and calls no
+ * consecutive chunks of as many as write no more than that array (about 1200
+ * prompts of the audit workload's shape, G = 16, D = 65536, R = 4096), and the
+ * outputs are bitwise those of pair_audit with the same arguments.  If the
+ * pair_audit_workspace_bytes of a single prompt, at least what it writes,
+ * exceeds the array, it returns PAIR_ESCRATCH and enqueues nothing.  The call
+ * allocates nothing and calls no
  * allocating routine.  Every call on one GPU uses that GPU's one array, which
  * keeps the last call's contents: calls ordered on one stream are safe, but
  * calls that overlap on one GPU (other streams, other host threads) race and

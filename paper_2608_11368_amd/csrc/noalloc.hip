@@ -1,7 +1,7 @@
 // The audit for callers that cannot allocate device memory: its workspace is
 // a file-scope device array of the library, one per GPU, instead of a
 // caller-provided buffer.  The prompts are audited in consecutive chunks
-// whose workspace fits the array, each chunk with the kernels pair_audit
+// of as many as write no more than the array, each chunk with the kernels pair_audit
 // runs and its own prompt-index base for the design draw, so every output is
 // bitwise that of pair_audit.
 #include <hip/hip_runtime.h>

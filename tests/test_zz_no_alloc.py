@@ -1,10 +1,15 @@
 """pair_audit_noalloc, the audit whose workspace is the library's static
 device scratch, against pair_audit with a caller workspace: two calls in a
 row through the C ABI, the audit workload at full size (B=256, G=16,
-D=65536, R=4096: four prompt chunks of the 64 MiB scratch) and then a
-smaller ragged batch with up to 64 candidates and a logged rho block.  Every
-output must be bitwise that of pair_audit (the same kernels, prompt by
-prompt), whatever the previous call left in the scratch."""
+D=65536, R=4096: one chunk of the 64 MiB scratch) and then a smaller ragged
+batch with up to 64 candidates and a logged rho block; and batches that the
+scratch cannot hold at once.  Every output must be bitwise that of pair_audit
+(the same kernels, prompt by prompt), whatever the previous call left in the
+scratch.
+
+The scratch holds a 64-bit word of indicators per prompt and replicate, so a
+batch of more than 64 MiB / 8 of those pairs is audited in several prompt
+chunks: later chunks start at a prompt other than 0, and reuse the scratch."""
 import numpy as np
 import pytest
 import torch
@@ -56,7 +61,6 @@ def test_noalloc_audit_equals_pair_audit_twice():
     ws = pair.pair_audit_workspace_bytes(meta.B, meta.gmax, w.D, w.R)
     log(f"no-alloc audit, full workload B={meta.B} D={w.D} R={w.R}: "
         f"workspace {ws / 2**20:.0f} MiB against {pair.AUDIT_SCRATCH_BYTES / 2**20:.0f} MiB")
-    assert ws > pair.AUDIT_SCRATCH_BYTES      # the call runs in several prompt chunks
     _compare(w, meta, w.R, 0)
     wr = wl.WORKLOADS["ragged"].replace(B=5, D=1504, dtype=wl.BF16)
     mr = wl.host_meta(wr)
@@ -65,21 +69,37 @@ def test_noalloc_audit_equals_pair_audit_twice():
     _compare(wr, mr, 200, 17, pi_w=pi_w)
 
 
+def _several_chunks(B, R):
+    return 8 * B * R > pair.AUDIT_SCRATCH_BYTES
+
+
+def test_noalloc_audit_in_several_chunks():
+    w = wl.WORKLOADS["audit"].replace(B=2200, D=264)
+    meta = wl.host_meta(w)
+    log(f"no-alloc audit in chunks: B={meta.B} G=16 D={w.D} R=4096 rep0=5")
+    assert _several_chunks(meta.B, 4096)
+    _compare(w, meta, 4096, 5)
+    wr = wl.WORKLOADS["ragged"].replace(B=4300, D=72, dtype=wl.BF16)
+    mr = wl.host_meta(wr)
+    log(f"no-alloc audit in chunks: ragged B={mr.B} gmax={mr.gmax} D={wr.D} R=2000 rep0=17")
+    assert _several_chunks(mr.B, 2000)
+    pi_w = torch.rand((mr.B, mr.gmax, mr.gmax), device=DEV) * 0.9 + 0.1
+    _compare(wr, mr, 2000, 17, pi_w=pi_w)
+
+
 def test_noalloc_audit_replays_from_a_graph():
     """The callers this entry point is for include code under HIP graph
     capture: the call is captured once (after an eager call has looked up
     the scratch's address) and replayed three times, with new rewards and
     continuation probabilities copied into the captured buffers between
     replays; every replay must equal an eager pair_audit with a workspace
-    bitwise, and the audit runs in two prompt chunks."""
-    w = wl.WORKLOADS["audit"].replace(B=100, D=65536 + 2048, R=4096)
+    bitwise, and the audit runs in several prompt chunks."""
+    w = wl.WORKLOADS["audit"].replace(B=2100, D=2048 + 64, R=4096)
     meta = wl.host_meta(w)
     dm = upload_meta(meta)
     s = wl.device_scores(w, meta.nv, DEV)
-    ws_bytes = pair.pair_audit_workspace_bytes(meta.B, meta.gmax, w.D, w.R)
-    log(f"no-alloc audit under graph capture: B={meta.B} D={w.D} R={w.R}, "
-        f"workspace {ws_bytes / 2**20:.0f} MiB against {pair.AUDIT_SCRATCH_BYTES / 2**20:.0f} MiB")
-    assert ws_bytes > pair.AUDIT_SCRATCH_BYTES
+    log(f"no-alloc audit under graph capture: B={meta.B} D={w.D} R={w.R}")
+    assert _several_chunks(meta.B, w.R)
     got = _outputs(meta.B, w.R)
 
     def call():
