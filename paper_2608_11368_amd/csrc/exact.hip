@@ -33,8 +33,6 @@ namespace pair {
 
 namespace {
 
-constexpr int kFinalThreads = 1024;
-
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -59,8 +57,12 @@ ExactLayout exact_layout(int64_t B, int32_t gmax, int64_t D) {
   const int64_t longer = L.ks == 1 ? 4 : 2;
   int64_t nsl = ceil_div(D, longer * round);
   if (B * nsl < 1024) {
-    nsl = ceil_div(1024, B);
-    if (nsl > ceil_div(D, round)) nsl = ceil_div(D, round);
+    int64_t more = ceil_div(1024, B);
+    if (more > ceil_div(D, round)) more = ceil_div(D, round);
+    // One workgroup adds a prompt's partials, 20 KB per slice of 64 rows: beyond
+    // 64 slices that takes longer than the Gram itself.
+    if (L.ks > 2 && more > 64) more = 64;
+    if (more > nsl) nsl = more;
   }
   if (nsl > ceil_div(8192, B)) nsl = ceil_div(8192, B);
   L.slice = ceil_div(ceil_div(D, nsl), round) * round;
@@ -97,6 +99,7 @@ __global__ __launch_bounds__(kGramThreads, gram_residency(KS)) void gram_kernel(
                     [](int, int) {});
 }
 
+template <int T>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
 #pragma unroll
@@ -105,12 +108,17 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   if (lane == 0) sh[wave] = v;
   __syncthreads();
   double t = 0.0;
-  for (int w = 0; w < kFinalThreads / kWave; ++w) t += sh[w];
+  for (int w = 0; w < T / kWave; ++w) t += sh[w];
   return t;
 }
 
-template <int KS, class Part>
-__global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
+// T threads: 1024, or 256 for groups of at most 16 and few slices (4 prompts of 8 at
+// D = 4096: 5.9 us with 1024, 4.6 us with 256; one prompt of 16 at D = 2^20, 512 slices:
+// 62 us with 256 threads adding them, 20 us with all).
+constexpr int64_t kFewSlices = 16;
+
+template <int KS, class Part, int T>
+__global__ __launch_bounds__(T) void exact_final_kernel(
     int64_t B, int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
     const float* __restrict__ rewards, const float* __restrict__ p,
     const float* __restrict__ pi_w, int32_t rule, float wmax, int64_t nsl,
@@ -119,12 +127,16 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
   constexpr int kRow = KP + 1;   // row stride in LDS: column walks spread over the banks
-  constexpr int kOwn = (kTiles + kFinalThreads / 256 - 1) / (kFinalThreads / 256);
+  constexpr int kGroups = T / 256;
+  constexpr int kOwn = (kTiles + kGroups - 1) / kGroups;
+  constexpr int kSplit = kTiles == 1 ? kGroups : 1;   // groups that share a tile's slices
+  constexpr int kFlight = kOwn == 1 ? 16 : 8;         // slices in flight
   __shared__ double K[KP * kRow];
   __shared__ double Ac[KP * kRow];   // A_ij: coefficient of s_i in v_ij; C_ij = A_ji
   __shared__ double X[KP * kRow];
   __shared__ double beta[KP], pd[KP], rd[KP];
-  __shared__ double sh[kFinalThreads / kWave];
+  __shared__ double sh[T / kWave];
+  __shared__ double split[kSplit > 1 ? kSplit - 1 : 1][256];
   const int64_t b = blockIdx.x;
   int64_t o0, g;
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g, d_status, threadIdx.x == 0)) return;
@@ -138,8 +150,9 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   }
   bool nonfinite = false;
   // Slice partials added in slice order; thread e of a group of 256 holds
-  // entry e of the group's tiles, eight slices of all of them in flight (one
-  // tile after the other took 12 us longer at 64 rows and 32 slices).
+  // entry e of the group's tiles, kFlight slices of all of them in flight (one
+  // tile after the other took 12 us longer at 64 rows and 32 slices).  A single
+  // tile's slices are shared by the groups.
   const int e = tid & 255;
   double sum[kOwn];
 #pragma unroll
@@ -147,26 +160,36 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   const Part* src = part + b * nsl * (kTiles * 256) + e;
   // Loads past the last slice or tile repeat it (a guarded load would wait for
   // its turn) and are not added.
-  for (int64_t s0 = 0; s0 < nsl; s0 += 8) {
-    Part v[kOwn][8];
+  const int team = __builtin_amdgcn_readfirstlane(tid / 256);
+  const int64_t s_lo = kSplit > 1 ? nsl * team / kSplit : 0;
+  const int64_t s_hi = kSplit > 1 ? nsl * (team + 1) / kSplit : nsl;
+  for (int64_t s0 = s_lo; s0 < s_hi; s0 += kFlight) {
+    Part v[kOwn][kFlight];
 #pragma unroll
     for (int u = 0; u < kOwn; ++u) {
-      int t = tid / 256 + u * (kFinalThreads / 256);
+      int t = kSplit > 1 ? 0 : team + u * kGroups;
       t = t < kTiles ? t : kTiles - 1;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int64_t sl = s0 + q < nsl ? s0 + q : nsl - 1;
+      for (int q = 0; q < kFlight; ++q) {
+        const int64_t sl = s0 + q < s_hi ? s0 + q : s_hi - 1;
         v[u][q] = src[(sl * kTiles + t) * 256];
       }
     }
 #pragma unroll
     for (int u = 0; u < kOwn; ++u)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sum[u] += s0 + q < nsl ? (double)v[u][q] : 0.0;
+      for (int q = 0; q < kFlight; ++q) sum[u] += s0 + q < s_hi ? (double)v[u][q] : 0.0;
+  }
+  if (kSplit > 1) {
+    if (team > 0) split[team - 1][e] = sum[0];
+    __syncthreads();
+    if (team == 0)
+#pragma unroll
+      for (int q = 1; q < kSplit; ++q) sum[0] += split[q - 1][e];
   }
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) {
-    const int t = tid / 256 + u * (kFinalThreads / 256);
+    const int t = team + u * kGroups;
     if (t >= kTiles) continue;
     int ta = 0, tc = 0;
 #pragma unroll
@@ -195,7 +218,7 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
 
   // Rule coefficients of every ordered pair, weights from the logged rho.
   bool bad = false;
-  for (int idx = tid; idx < KP * KP; idx += kFinalThreads) {
+  for (int idx = tid; idx < KP * KP; idx += T) {
     const int i = idx / KP, j = idx - i * KP;
     double a = 0.0;
     if (i != j && i < gi && j < gi) {
@@ -228,7 +251,7 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   // X_ij = p_j C_ij off the diagonal and X_ii = sum_j p_j A_ij, the
   // coefficients of sum_j p_j v_ij; the row sums by 16 lanes per row.
   const double M = 0.5 * (double)gi * (double)(gi - 1);
-  for (int idx = tid; idx < KP * KP; idx += kFinalThreads) {
+  for (int idx = tid; idx < KP * KP; idx += T) {
     const int i = idx / KP, j = idx - i * KP;
     if (i != j) X[i * kRow + j] = pd[j] * Ac[j * kRow + i];   // zero past the group
   }
@@ -252,7 +275,7 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
 
   // beta^T K beta and the pair terms.
   double bk = 0.0, tr = 0.0;
-  for (int idx = tid; idx < gi * gi; idx += kFinalThreads) {
+  for (int idx = tid; idx < gi * gi; idx += T) {
     const int i = idx / gi, j = idx - i * gi;
     bk += beta[i] * beta[j] * K[i * kRow + j];
     if (j <= i) continue;
@@ -269,7 +292,7 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
   // past the group are zero.
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int col = lane & 15, grp = lane >> 4;
-  for (int t = wave; t < KS * KS; t += kFinalThreads / kWave) {
+  for (int t = wave; t < KS * KS; t += T / kWave) {
     const int r0 = 16 * (t / KS), c0 = 16 * (t % KS);
     f64x4_t y = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -282,8 +305,8 @@ __global__ __launch_bounds__(kFinalThreads) void exact_final_kernel(
       tr += pd[i] * (1.0 - pd[i]) * y[v] * X[i * kRow + c0 + col];
     }
   }
-  const double bb = block_sum(bk, sh);
-  const double tt = block_sum(tr, sh);
+  const double bb = block_sum<T>(bk, sh);
+  const double tt = block_sum<T>(tr, sh);
   if (tid == 0) {
     const double b2 = bb > 0.0 ? bb : 0.0;
     mse[b] = b2 + tt / (M * M);
@@ -311,11 +334,16 @@ int launch_audit_exact(int64_t B, int64_t nv, int32_t gmax, const int64_t* offse
                      stream, nv, gmax, offsets, D, s, ld, L.nsl, L.slice,                        \
                      static_cast<PART_*>(workspace))
 #define PAIR_FINAL(KS_, PART_)                                                                   \
-  hipLaunchKernelGGL((exact_final_kernel<KS_, PART_>), dim3((unsigned)B), dim3(kFinalThreads), 0, \
-                     stream, B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, L.nsl,          \
+  if (KS_ == 1 && L.nsl <= kFewSlices)                                                           \
+    PAIR_FINAL_T(KS_, PART_, (KS_ == 1 ? 256 : 1024));                                           \
+  else                                                                                           \
+    PAIR_FINAL_T(KS_, PART_, 1024)
+#define PAIR_FINAL_T(KS_, PART_, T_)                                                             \
+  hipLaunchKernelGGL((exact_final_kernel<KS_, PART_, T_>), dim3((unsigned)B), dim3(T_), 0, stream, \
+                     B, nv, gmax, offsets, rewards, p, pi_w, rule, wmax, L.nsl,                  \
                      static_cast<const PART_*>(workspace), mse, bias_norm, gram, d_status)
 #define PAIR_OF(LAUNCH_, KS_) \
-  if (L.wide) LAUNCH_(KS_, double); else LAUNCH_(KS_, float)
+  if (L.wide) { LAUNCH_(KS_, double); } else { LAUNCH_(KS_, float); }
   switch (L.ks) {
     case 1: PAIR_OF(PAIR_GRAM, 1); break;
     case 2: PAIR_OF(PAIR_GRAM, 2); break;
@@ -331,6 +359,7 @@ int launch_audit_exact(int64_t B, int64_t nv, int32_t gmax, const int64_t* offse
   }
 #undef PAIR_OF
 #undef PAIR_GRAM
+#undef PAIR_FINAL_T
 #undef PAIR_FINAL
   return hipGetLastError() == hipSuccess ? PAIR_OK : PAIR_EHIP;
 }
