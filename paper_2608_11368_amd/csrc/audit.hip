@@ -36,6 +36,8 @@
 //                   quadratic form (fp64 matrix instructions).
 //  4. audit_final   MSE, bias, or the mean cosine; prompts whose bias nearly
 //                   cancels in K are taken from the score rows.
+#include <type_traits>
+
 #include "common.hpp"
 #include "gram.hpp"
 #include "launch.hpp"
@@ -45,7 +47,7 @@ namespace pair {
 namespace {
 
 constexpr int kEvalThreads = 256;
-constexpr int kTableThreads = 256;
+constexpr int kTableThreads = 1024;   // at most
 constexpr int kFinalThreads = 256;
 constexpr int64_t kFinalCols = 8 * kFinalThreads;   // columns of an audit_final step
 constexpr int64_t kMaxSlices = 128;   // score-column slices per prompt at most
@@ -251,30 +253,36 @@ __device__ __forceinline__ int frag_place64(int kp, int i, int j) {
   return ((i >> 4) * (kp / 4) + step) * kWave + lane;
 }
 
-// One workgroup per prompt for the edge table and one per tile of K.
+// One workgroup per prompt for the edge table and one per tile of K, of 256
+// threads, or of four times as many for rows of more than kTableSlices slices:
+// groups of 256 then add a quarter of the slices each (one prompt of 16 at D = 2^20, 128
+// slices: 36 us with 256 threads, 9 us so).
+constexpr int64_t kTableSlices = 16;
+
 template <int KS>
 __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
     int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets,
     const float* __restrict__ rewards, const float* __restrict__ p, const float* __restrict__ pi_w,
-    int32_t rule, float wmax, int64_t nsl, int skip_equal, const double* __restrict__ part,
+    int32_t rule, float wmax, int64_t nsl, int together, int skip_equal, const double* __restrict__ part,
     const int32_t* __restrict__ gex, double* __restrict__ K, float* __restrict__ wt,
     float* __restrict__ vt, double* __restrict__ a_out, int32_t* __restrict__ flag,
     int32_t* __restrict__ count, int32_t* d_status) {
   constexpr int KP = 16 * KS;
   constexpr int kTiles = gram_tiles(KS);
   __shared__ float pl[KP], rl[KP];
-  const int64_t b = blockIdx.x / (kTiles + 1);
-  const int t = (int)(blockIdx.x - b * (kTiles + 1)) - 1;
+  __shared__ double quarter[kTableThreads / 256 - 1][256];
+  const int64_t b = together ? blockIdx.x : blockIdx.x / (kTiles + 1);
+  const int t = together ? 0 : (int)(blockIdx.x - b * (kTiles + 1)) - 1;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   int64_t o0, g64;
-  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, d_status, t < 0 && tid == 0)) return;
+  if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, d_status, (together || t < 0) && tid == 0))
+    return;
   const int g = (int)g64;
 
-  if (t >= 0) {
-    // Thread e holds entry e of the tile; the slices are added in order,
-    // sixteen loads in flight.  The stream leaves no partials for a prompt
+  if (t >= 0 && !(skip_equal && !rewards_differ(rewards + o0, g, lane))) {
+    // Thread e of a group holds entry e of the tile; the slices are added in
+    // order, sixteen loads in flight.  The stream leaves no partials for a prompt
     // of equal rewards, and nothing reads its K.
-    if (skip_equal && !rewards_differ(rewards + o0, g, lane)) return;
     int a = 0, c = 0;
 #pragma unroll
     for (int x = 0; x < KS; ++x)
@@ -284,25 +292,28 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
           a = x;
           c = y;
         }
-    const int i = 16 * a + 4 * (tid >> 6) + (tid & 3), j = 16 * c + ((tid >> 2) & 15);
-    const double* src = part + (b * nsl * kTiles + t) * 256 + tid;
+    const int e = tid & 255, grp = __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int groups = (int)blockDim.x >> 8;
+    const int i = 16 * a + 4 * (e >> 6) + (e & 3), j = 16 * c + ((e >> 2) & 15);
+    const int64_t s_lo = nsl * grp / groups, s_hi = nsl * (grp + 1) / groups;
+    const double* src = part + (b * nsl * kTiles + t) * 256 + e;
     const int32_t* gx = gex + b * nsl * (KP + 1);
     double k = 0.0;
     const bool inside = 16 * c < g;   // uniform; entries past g inside a block are 0
     // Loads past the last slice repeat it (a guarded load would wait for its
     // turn) and are not added.
-    for (int64_t s0 = 0; inside && s0 < nsl; s0 += 16) {
+    for (int64_t s0 = s_lo; inside && s0 < s_hi; s0 += 16) {
       double v[16];
       int32_t scaled[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const int64_t sl = s0 + q < nsl ? s0 + q : nsl - 1;
+        const int64_t sl = s0 + q < s_hi ? s0 + q : s_hi - 1;
         v[q] = src[sl * (kTiles * 256)];
         scaled[q] = gx[sl * (KP + 1) + KP];
       }
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        if (s0 + q >= nsl) break;
+        if (s0 + q >= s_hi) break;
         double x = v[q];
         if (skip_equal && scaled[q] != 0) {   // else the exponents were not written
           const int32_t* row = gx + (s0 + q) * (KP + 1);
@@ -312,11 +323,18 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
         k += x;
       }
     }
-    if (!skip_equal && !isfinite(k)) raise_status(d_status, PAIR_ST_NONFINITE);
-    K[b * (KP * KP) + frag_place64(KP, i, j)] = k;
-    if (a != c) K[b * (KP * KP) + frag_place64(KP, j, i)] = k;
-    return;
+    if (groups > 1) {
+      if (grp > 0) quarter[grp - 1][e] = k;
+      __syncthreads();
+    }
+    if (grp == 0) {
+      for (int q = 1; q < groups; ++q) k += quarter[q - 1][e];
+      if (!skip_equal && !isfinite(k)) raise_status(d_status, PAIR_ST_NONFINITE);
+      K[b * (KP * KP) + frag_place64(KP, i, j)] = k;
+      if (a != c) K[b * (KP * KP) + frag_place64(KP, j, i)] = k;
+    }
   }
+  if (t >= 0 && !together) return;
 
   if (wave == 0) {
     const bool vert = lane < g;
@@ -337,7 +355,7 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
   }
   __syncthreads();
   bool bad_rho = false;
-  for (int idx = tid; idx < KP * KP; idx += kTableThreads) {
+  for (int idx = tid; idx < KP * KP; idx += (int)blockDim.x) {
     const int fl = idx & (kWave - 1), blk = idx / kWave;
     const int i = 16 * (blk / (KP / 4)) + (fl & 15), j = frag_column(blk % (KP / 4), fl);
     float w = 0.0f, v = 0.0f;
@@ -446,8 +464,9 @@ __device__ __forceinline__ void fold_table(const float* table, const uint32_t (&
     }
 }
 
-template <int KS, bool COS>
-__global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
+// T threads: kEvalThreads, one wave where groups of up to 16 have 64 replicates or fewer.
+template <int KS, bool COS, int T>
+__global__ __launch_bounds__(T) void audit_eval_kernel(
     int64_t nv, int32_t gmax, const int64_t* __restrict__ offsets, int32_t rule, int64_t R,
     int64_t nchunk, int rounds, const double* __restrict__ K, const float* __restrict__ wt,
     const float* __restrict__ vt, const double* __restrict__ a_full,
@@ -456,7 +475,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     int32_t* __restrict__ edge_count, double* __restrict__ target_norm) {
   constexpr int KP = 16 * KS;
   constexpr int NC = KS <= 2 ? 4 : 2;   // blocks of 16 replicates at once
-  constexpr int kWaves = kEvalThreads / kWave;
+  constexpr int kWaves = T / kWave;
   __shared__ __align__(16) double Ks[KP * KP];
   __shared__ __align__(16) float Ws[KP * KP];
   __shared__ double wsum[kWaves][KP];
@@ -485,9 +504,9 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
 #pragma unroll
     for (int v = 0; v < 4; ++v) af[ib][v] = a_full[b * KP + 16 * ib + 4 * grp + v];
   const double* Kb = K + b * (KP * KP);
-  for (int idx = 2 * tid; idx < KP * KP; idx += 2 * kEvalThreads)
+  for (int idx = 2 * tid; idx < KP * KP; idx += 2 * T)
     *reinterpret_cast<double2*>(Ks + idx) = *reinterpret_cast<const double2*>(Kb + idx);
-  for (int idx = 4 * tid; idx < KP * KP; idx += 4 * kEvalThreads)
+  for (int idx = 4 * tid; idx < KP * KP; idx += 4 * T)
     *reinterpret_cast<float4*>(Ws + idx) =
         *reinterpret_cast<const float4*>(wt + b * (KP * KP) + idx);
   const bool live = flag[b] != 0;
@@ -515,9 +534,9 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
     }
     return;   // audit_final looks at the flag too
   }
-  if (tid <= PAIR_GMAX_LIMIT) {
-    recip[tid] = tid > 0 ? 1.0 / (double)tid : 0.0;
-    recip32[tid] = rule != PAIR_RULE_MARGINAL ? (float)recip[tid] : 0.0f;   // not centred
+  for (int k = tid; k <= PAIR_GMAX_LIMIT; k += T) {
+    recip[k] = k > 0 ? 1.0 / (double)k : 0.0;
+    recip32[k] = rule != PAIR_RULE_MARGINAL ? (float)recip[k] : 0.0f;   // not centred
   }
   __syncthreads();
   const double inv_pool = 1.0 / (double)(g * (g - 1));
@@ -597,7 +616,7 @@ __global__ __launch_bounds__(kEvalThreads) void audit_eval_kernel(
 #pragma unroll
     for (int v = 0; v < 4; ++v) dsum[ib][v] = 0.0;
   double esum = 0.0;
-  const int steps = rounds * (4 / NC);
+  const int steps = first < R ? rounds * (4 / NC) : 0;   // waves past R have no replicates
 #pragma unroll 1
   for (int t = 0; t < steps; ++t) {
     const int64_t r0 = first + (int64_t)t * (16 * NC) + (lane & 15);
@@ -926,14 +945,28 @@ int run_audit(const AuditLayout& L, const AuditArgs& A) {
                      reinterpret_cast<uint16_t*>(bits), A.edge_count != nullptr ? 1 : 0,
                      A.d_status);
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-  hipLaunchKernelGGL((audit_tables_kernel<KS>), dim3((unsigned)table_grid), dim3(kTableThreads), 0,
+  // Groups of up to 16 have one tile: more prompts than the chip holds of both
+  // kinds of workgroups at once take one workgroup for both (2000 prompts:
+  // 12.9 us in two, 9.5 us in one; 256 prompts: 4.9 us in two).
+  const bool together = KS == 1 && table_grid > 8 * (int64_t)device_cu_count();
+  hipLaunchKernelGGL((audit_tables_kernel<KS>), dim3((unsigned)(together ? A.B : table_grid)),
+                     dim3(L.nsl > kTableSlices ? kTableThreads : 256), 0,
                      A.stream, A.nv, A.gmax, A.offsets, A.rewards, A.p, A.pi_w, A.rule, A.wmax,
-                     L.nsl, own, part, gex, K, wt, vt, a, flag, count, A.d_status);
+                     L.nsl, together ? 1 : 0, own, part, gex, K, wt, vt, a, flag, count, A.d_status);
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
-  hipLaunchKernelGGL((audit_eval_kernel<KS, COS>), dim3((unsigned)eval_grid), dim3(kEvalThreads), 0,
-                     A.stream, A.nv, A.gmax, A.offsets, A.rule, A.R, L.nchunk, L.rounds, K, wt, vt,
-                     a, flag, bits, epart, dpart, A.rep_sqerr, A.edge_count,
-                     COS ? A.second : nullptr);
+  auto eval = [&](auto threads) {
+    constexpr int T = decltype(threads)::value;
+    hipLaunchKernelGGL((audit_eval_kernel<KS, COS, T>), dim3((unsigned)eval_grid), dim3(T), 0,
+                       A.stream, A.nv, A.gmax, A.offsets, A.rule, A.R, L.nchunk, L.rounds, K, wt, vt,
+                       a, flag, bits, epart, dpart, A.rep_sqerr, A.edge_count,
+                       COS ? A.second : nullptr);
+  };
+  // A chunk of at most 64 replicates and small tables are one wave's (2000 prompts of 4,
+  // R = 32: 13.5 us with four, 8.3 us with one).
+  if (KS == 1 && A.R <= kWave)
+    eval(std::integral_constant<int, KS == 1 ? kWave : kEvalThreads>{});
+  else
+    eval(std::integral_constant<int, kEvalThreads>{});
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
   hipLaunchKernelGGL((audit_final_kernel<COS>), dim3((unsigned)final_grid), dim3(kFinalThreads), 0,
                      A.stream, A.nv, A.gmax, L.kp, A.offsets, A.D, s, A.ld, (int)nbias, L.bslice,
