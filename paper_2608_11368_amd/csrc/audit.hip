@@ -56,7 +56,7 @@ constexpr int64_t kDrawRun = 512;     // replicates a stream workgroup draws at 
 
 // Groups that may exceed 48: the fp64 sums of ten tiles leave no registers for
 // the generator beside them, so the prompt's first workgroups draw and the others
-// stream (B = 64, G in 2..64, D = 20011, R = 1000: 46 us, with both in one 54 us).
+// stream (128 prompts of 64, D = 65536, R = 500: 183 us, with both in one 203 us).
 __host__ __device__ constexpr bool draws_apart(int ks) { return ks == 4; }
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -253,11 +253,12 @@ __device__ __forceinline__ int frag_place64(int kp, int i, int j) {
   return ((i >> 4) * (kp / 4) + step) * kWave + lane;
 }
 
-// One workgroup per prompt for the edge table and one per tile of K, of 256
-// threads, or of four times as many for rows of more than kTableSlices slices:
-// groups of 256 then add a quarter of the slices each (one prompt of 16 at D = 2^20, 128
-// slices: 36 us with 256 threads, 9 us so).
-constexpr int64_t kTableSlices = 16;
+// One workgroup per prompt for the edge table and one per tile of K.  Rows of
+// at least kTableSlices slices are summed in quarters, and the quarters in order, by 256
+// threads one after the other, or by 1024 at once where the workgroups are few
+// (one prompt of 16 at D = 2^20, 128 slices: 36 us with 256 threads, 9 us so; 128
+// prompts of 64, 32 slices: 18 us with 256, 30 us with 1024).
+constexpr int64_t kTableSlices = 64;
 
 template <int KS>
 __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
@@ -293,35 +294,39 @@ __global__ __launch_bounds__(kTableThreads) void audit_tables_kernel(
           c = y;
         }
     const int e = tid & 255, grp = __builtin_amdgcn_readfirstlane(tid >> 8);
-    const int groups = (int)blockDim.x >> 8;
+    const int groups = (int)blockDim.x >> 8, parts = nsl >= kTableSlices ? 4 : 1;
     const int i = 16 * a + 4 * (e >> 6) + (e & 3), j = 16 * c + ((e >> 2) & 15);
-    const int64_t s_lo = nsl * grp / groups, s_hi = nsl * (grp + 1) / groups;
     const double* src = part + (b * nsl * kTiles + t) * 256 + e;
     const int32_t* gx = gex + b * nsl * (KP + 1);
     double k = 0.0;
     const bool inside = 16 * c < g;   // uniform; entries past g inside a block are 0
-    // Loads past the last slice repeat it (a guarded load would wait for its
-    // turn) and are not added.
-    for (int64_t s0 = s_lo; inside && s0 < s_hi; s0 += 16) {
-      double v[16];
-      int32_t scaled[16];
+    for (int u = grp; inside && u < parts; u += groups) {
+      const int64_t s_lo = nsl * u / parts, s_hi = nsl * (u + 1) / parts;
+      double sum = 0.0;
+      // Loads past the last slice repeat it (a guarded load would wait for its
+      // turn) and are not added.
+      for (int64_t s0 = s_lo; s0 < s_hi; s0 += 16) {
+        double v[16];
+        int32_t scaled[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int64_t sl = s0 + q < s_hi ? s0 + q : s_hi - 1;
-        v[q] = src[sl * (kTiles * 256)];
-        scaled[q] = gx[sl * (KP + 1) + KP];
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        if (s0 + q >= s_hi) break;
-        double x = v[q];
-        if (skip_equal && scaled[q] != 0) {   // else the exponents were not written
-          const int32_t* row = gx + (s0 + q) * (KP + 1);
-          // rows past the prompt's own blocks have no exponent
-          x = i < g && j < g ? ldexp(x, row[i] + row[j]) : 0.0;
+        for (int q = 0; q < 16; ++q) {
+          const int64_t sl = s0 + q < s_hi ? s0 + q : s_hi - 1;
+          v[q] = src[sl * (kTiles * 256)];
+          scaled[q] = gx[sl * (KP + 1) + KP];
         }
-        k += x;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          if (s0 + q >= s_hi) break;
+          double x = v[q];
+          if (skip_equal && scaled[q] != 0) {   // else the exponents were not written
+            const int32_t* row = gx + (s0 + q) * (KP + 1);
+            // rows past the prompt's own blocks have no exponent
+            x = i < g && j < g ? ldexp(x, row[i] + row[j]) : 0.0;
+          }
+          sum += x;
+        }
       }
+      k += sum;
     }
     if (groups > 1) {
       if (grp > 0) quarter[grp - 1][e] = k;
@@ -949,8 +954,9 @@ int run_audit(const AuditLayout& L, const AuditArgs& A) {
   // kinds of workgroups at once take one workgroup for both (2000 prompts:
   // 12.9 us in two, 9.5 us in one; 256 prompts: 4.9 us in two).
   const bool together = KS == 1 && table_grid > 8 * (int64_t)device_cu_count();
+  const bool few = L.nsl >= kTableSlices && table_grid <= 2 * (int64_t)device_cu_count();
   hipLaunchKernelGGL((audit_tables_kernel<KS>), dim3((unsigned)(together ? A.B : table_grid)),
-                     dim3(L.nsl > kTableSlices ? kTableThreads : 256), 0,
+                     dim3(few ? kTableThreads : 256), 0,
                      A.stream, A.nv, A.gmax, A.offsets, A.rewards, A.p, A.pi_w, A.rule, A.wmax,
                      L.nsl, together ? 1 : 0, own, part, gex, K, wt, vt, a, flag, count, A.d_status);
   if (hipGetLastError() != hipSuccess) return PAIR_EHIP;
