@@ -51,7 +51,7 @@ constexpr int kTableThreads = 1024;   // at most
 constexpr int kFinalThreads = 256;
 constexpr int64_t kFinalCols = 8 * kFinalThreads;   // columns of an audit_final step
 constexpr int64_t kMaxSlices = 128;   // score-column slices per prompt at most
-constexpr int64_t kMaxBiasSlices = 32;
+constexpr int64_t kMaxBiasSlices = 16;
 constexpr int64_t kDrawRun = 512;     // replicates a stream workgroup draws at most, about
 
 // Groups that may exceed 48: the fp64 sums of ten tiles leave no registers for
@@ -768,13 +768,15 @@ __global__ __launch_bounds__(T) void audit_eval_kernel(
 //    column in fp64.  Every workgroup of a prompt decides for itself (the
 //    form takes it as long as asking another), and the last of them adds the slices in order.
 //    G = 16, D = 4096, R = 1000, a common component of 100 times the rest: the form alone
-//    is off by 1e-4 of the norm, so 1e-6.  B = 256, G = 16, D = 65536, R = 4096: 4.6 us
-//    with the form alone and a wave per prompt, 6.6 us so, and 190 us where every prompt is read again.
+//    is off by 1e-4 of the norm, so 1e-6.  64 registers, so that eight workgroups
+//    share a CU: B = 256, G = 16, D = 65536, R = 4096 4.6 us (with 130 registers
+//    6.6), 128 prompts of 64 with 16 slices 8.6 (32 slices and 130 registers: 18.5), and
+//    190 us where every prompt of the former is read again.
 // ---------------------------------------------------------------------------
 constexpr double kCancel = 64.0;
 
 template <bool COS>
-__global__ __launch_bounds__(kFinalThreads) void audit_final_kernel(
+__global__ __launch_bounds__(kFinalThreads, 8) void audit_final_kernel(
     int64_t nv, int32_t gmax, int kp, const int64_t* __restrict__ offsets, int64_t D,
     const uint16_t* __restrict__ scores, int64_t ld, int nbias, int64_t bslice, int64_t R,
     int64_t nchunk, const double* __restrict__ K, const int32_t* __restrict__ flag,
@@ -842,7 +844,7 @@ __global__ __launch_bounds__(kFinalThreads) void audit_final_kernel(
     return;
   }
 
-  // Eight columns per thread and step, eight rows in flight.  Rows past the
+  // Eight columns per thread and step, four rows in flight.  Rows past the
   // group repeat the last one, with the factor 0.
   const uint16_t* rows = scores + o0 * ld;
   const int64_t c_lo = slot * bslice, c_hi = c_lo + bslice < D ? c_lo + bslice : D;
@@ -852,15 +854,15 @@ __global__ __launch_bounds__(kFinalThreads) void audit_final_kernel(
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = 0.0;
     if (c + 8 <= c_hi) {
-      for (int i0 = 0; i0 < g; i0 += 8) {
-        uint4 v[8];
+      for (int i0 = 0; i0 < g; i0 += 4) {
+        uint4 v[4];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int s = 0; s < 4; ++s) {
           const int i = i0 + s < g ? i0 + s : g - 1;
           v[s] = load_nt16(rows + (int64_t)i * ld + c);
         }
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int s = 0; s < 4; ++s) {
           const double f = dl[i0 + s];
           const uint32_t w[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
 #pragma unroll
