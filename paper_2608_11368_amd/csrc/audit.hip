@@ -483,6 +483,7 @@ __global__ __launch_bounds__(T) void audit_eval_kernel(
   constexpr int kWaves = T / kWave;
   __shared__ __align__(16) double Ks[KP * KP];
   __shared__ __align__(16) float Ws[KP * KP];
+  __shared__ __align__(16) float Vs[KP * KP];   // of the self-normalised rule
   __shared__ double wsum[kWaves][KP];
   __shared__ double red[kWaves];
   __shared__ double recip[PAIR_GMAX_LIMIT + 1];
@@ -514,6 +515,10 @@ __global__ __launch_bounds__(T) void audit_eval_kernel(
   for (int idx = 4 * tid; idx < KP * KP; idx += 4 * T)
     *reinterpret_cast<float4*>(Ws + idx) =
         *reinterpret_cast<const float4*>(wt + b * (KP * KP) + idx);
+  if (rule == PAIR_RULE_SELFNORM)
+    for (int idx = 4 * tid; idx < KP * KP; idx += 4 * T)
+      *reinterpret_cast<float4*>(Vs + idx) =
+          *reinterpret_cast<const float4*>(vt + b * (KP * KP) + idx);
   const bool live = flag[b] != 0;
   int64_t o0, g64;
   if (!prompt_bounds(offsets, b, nv, 2, gmax, &o0, &g64, nullptr, false)) return;
@@ -646,7 +651,7 @@ __global__ __launch_bounds__(T) void audit_eval_kernel(
       for (int cb = 0; cb < NC; ++cb)
         inv[cb] = k[cb] >= 2 ? recip[k[cb]] * recip[k[cb] - 1] : 0.0;
     } else if (rule == PAIR_RULE_SELFNORM) {
-      fold_table<KS, NC>(vt + b * (KP * KP), nib, nb, lane, C);
+      fold_table<KS, NC>(Vs, nib, nb, lane, C);
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) {
         double n2 = 0.0;
