@@ -28,9 +28,9 @@
 //                   J^(r) of each replicate as a 64-bit word.  Prompts whose
 //                   rewards are all equal have delta_r = 0 in every
 //                   replicate: their rows are not read.
-//  2. audit_tables  one workgroup per prompt: the slice partials added in
-//                   order into K (fp64), the rule's edge table, the target's
-//                   coefficients, the status checks.
+//  2. audit_tables  workgroups per prompt: one per tile of K, the slice partials
+//                   added in order (fp64), and one for the rule's edge table,
+//                   the target's coefficients and the status checks.
 //  3. audit_eval    64 replicates per wave: the fold of their indicators over
 //                   the edge table (fp32 matrix instructions) and the
 //                   quadratic form (fp64 matrix instructions).
@@ -92,10 +92,11 @@ AuditLayout audit_layout(int64_t B, int32_t gmax, int64_t D, int64_t R) {
   else
     L.slots = L.nsl > ceil_div(R, kDrawRun) ? L.nsl : ceil_div(R, kDrawRun);
   // A wave's first 64 replicates cost the latency of its tables, so with many
-  // it takes twice 64 (28.5 us against 26.4 us at B = 256, G = 16, R = 4096;
-  // four times: 28.1 us, the last workgroups run alone).  Groups above 32 have
-  // work enough in 64 (21 us against 34 us at B = 64, G in 2..64, R = 1000).  By
-  // R and gmax alone: the sums' order is the prompt's own.
+  // it takes twice 64 (one round and two, us: B = 256, G = 16, R = 4096 29.4 and 28.9; B = 64,
+  // G = 32 22.8 and 20.8; four rounds leave the last workgroups alone).  A few prompts
+  // lose by it (B = 4: 5.4 and 7.0).  Groups above 32 have work enough in 64 (21 us
+  // against 34 us at B = 64, G in 2..64, R = 1000).  By R and gmax alone: the sums'
+  // order is the prompt's own.
   L.rounds = R >= 2048 && L.ks <= 2 ? 2 : 1;
   L.nchunk = ceil_div(R, (int64_t)L.rounds * kEvalThreads);
   const int64_t nbias = L.nsl < kMaxBiasSlices ? L.nsl : kMaxBiasSlices;
